@@ -582,8 +582,14 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     return SPEC_OK;
   };
   HIP_TRY(launch_rmsnorm(d_x, (const bf16*)w->attn_norm[0], d_h, N, H, cfg->rms_eps, s), "rmsnorm");
+  const GemmPlan p_qkv = plan_gemm(EPI_QKV, N, (nq + 2 * nkv) * hd, H, nq * hd, nkv * hd, false);
+  const GemmPlan p_o = plan_gemm(EPI_RESID, N, H, nq * hd, H, 0, true);
+  const GemmPlan p_gate_up = plan_gemm(EPI_GATE_UP, N, 2 * F, H, F, F, false);
+  const GemmPlan p_down = plan_gemm(EPI_RESID, N, H, F, H, 0, true);
+  const GemmPlan p_head = plan_gemm(EPI_ARGMAX, N, V, H, V, 0, false);
   for (int l = 0; l < L; ++l) {
     GemmArgs g = ga;
+    g.plan = p_qkv;
     g.A = d_h;
     g.K = H;
     g.B0 = (const bf16*)w->wq[l];
@@ -598,6 +604,7 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     aa.layer = l;
     HIP_TRY(timed(SPEC_K_ATTENTION, s, [&] { return launch_attention(aa, s); }), "attention");
     g = ga;
+    g.plan = p_o;
     g.A = d_o;
     g.K = nq * hd;
     g.B0 = (const bf16*)w->wo[l];
@@ -605,6 +612,7 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     g.x = d_x;
     if (int rc = resid_then_norm(SPEC_K_GEMM_O, g, w->ffn_norm[l], "o gemm")) return rc;
     g = ga;
+    g.plan = p_gate_up;
     g.A = d_h;
     g.K = H;
     g.B0 = (const bf16*)w->w_gate[l];
@@ -614,6 +622,7 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     g.act_out = d_act;
     HIP_TRY(timed(SPEC_K_GEMM_GATE_UP, s, [&] { return launch_gemm(EPI_GATE_UP, g, s); }), "gate/up gemm");
     g = ga;
+    g.plan = p_down;
     g.A = d_act;
     g.K = F;
     g.B0 = (const bf16*)w->w_down[l];
@@ -624,6 +633,7 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
   }
   {
     GemmArgs g = ga;
+    g.plan = p_head;
     g.A = d_h;
     g.K = H;
     g.B0 = (const bf16*)w->lm_head;
@@ -633,7 +643,7 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     g.logits = D.logits ? D.logits : sampled ? (float*)(ws + ly.logits) : nullptr;
     HIP_TRY(timed(SPEC_K_LM_HEAD, s, [&] { return launch_gemm(EPI_ARGMAX, g, s); }), "lm head");
   }
-  HIP_TRY(launch_argmax_reduce(d_lmv, d_lmi, N, gemm_parts(V, N, H), d_arg, D.argmax, s), "argmax");
+  HIP_TRY(launch_argmax_reduce(d_lmv, d_lmi, N, V / 64, d_arg, D.argmax, s), "argmax");
   if (sampled) {
     const float* logits = D.logits ? D.logits : (const float*)(ws + ly.logits);
     HIP_TRY(timed(SPEC_K_ACCEPT, s, [&] {

@@ -101,7 +101,15 @@ int set_error(int code, const char* msg);
 
 enum GemmEpilogue { EPI_QKV = 0, EPI_RESID = 1, EPI_GATE_UP = 2, EPI_ARGMAX = 3 };
 
+// How a product runs: its kernel and tile, and the K splits.
+enum GemmShape { GEMM_FEW_ROWS, GEMM_64x64, GEMM_64x128, GEMM_128x128, GEMM_256x128, GEMM_256x256 };
+struct GemmPlan {
+  GemmShape shape;
+  int splits;
+};
+
 struct GemmArgs {
+  GemmPlan plan;          // plan_gemm() for this product
   const bf16* A;          // [M][K] activations
   int M, K;
   // Weight segments (row-major [rows][K]); virtual columns run through them
@@ -121,13 +129,10 @@ struct GemmArgs {
   // EPI_GATE_UP
   bf16* act_out;          // [M][ffn]
   // EPI_ARGMAX
-  float* part_val;        // [M][gemm_parts(N, M, K)]
+  float* part_val;        // [M][N / 64]
   int32_t* part_idx;
   float* logits;          // optional [M][N]
-  // Split-K scratch (gemm_partial_bytes() bytes; NULL disables splitting) and
-  // the split count the launcher picked.
-  float* partial;
-  int ksplit;
+  float* partial;         // split-K scratch, gemm_partial_bytes() bytes
   // EPI_RESID: the RMSNorm that follows the product (norm_out = bf16 of
   // x / rms(x) * norm_gain, row-major [M][N]); NULL: none.  When the product
   // is split over K, the launcher fuses the norm into the split-K reduction
@@ -139,9 +144,9 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(int epi, const GemmArgs& a, hipStream_t s);
-// Number of (max, index) partials per row the EPI_ARGMAX launch for an
-// [M x N] product with inner dimension K writes.
-int gemm_parts(int N, int M, int K);
+// The plan of an [M x N] product with inner dimension K and weight segments of
+// n0, n1, ... rows; norm: an RMSNorm follows.
+GemmPlan plan_gemm(int epi, int M, int N, int K, int n0, int n1, bool norm);
 // Bytes of split-K partial storage launch_gemm may use through GemmArgs::partial.
 size_t gemm_partial_bytes();
 // Device address of the current device's static scratch (noalloc.hip).

@@ -11,27 +11,20 @@
 //   EPI_ARGMAX   LM head: per row, the (max, lowest index) over each wave's
 //                column slab, optionally also the fp32 logits
 //
-// Three kernels, chosen by pick_tile() and skinny_max_rows():
-//   * many rows (over 128): 256 x 256 and 256 x 128 tiles whose two wave groups
-//     run in opposite phases (see there);
-//   * few rows: one work-group per 16 weight rows (see there);
-//   * in between, the ring kernel: one work-group of 4 waves in a WM x WN grid,
-//     output tile BM x BN (128 x 128 with 4 stages, 64 x 256 and 32 x 256 with
-//     3, where the weights are streamed), each wave BM/WM x BN/WN built from
-//     32 x 32 v_mfma_f32_32x32x16_bf16 blocks, K step 64:
-//   * operand tiles move HBM/L2 -> LDS with global_load_lds_dwordx4 (no
-//     register staging) into a ring of NS stages; the next NS-1 K steps are
-//     in flight while the current one is multiplied, and one barrier per K
-//     step both publishes the next stage and frees the oldest slot.  The
-//     barrier waits only for this wave's LDS reads and for the loads of the
-//     next stage (vmcnt counts the later stages out), never for the whole
-//     ring.  A stage's wave-loads are issued in four parts between the MFMA
-//     blocks, with their LDS destinations in scalar registers;
-//   * each wave-load writes 1 KB = 8 tile rows of 128 bytes; the 16-byte chunk
-//     index of row r is XOR-ed with (r >> 1) & 7, which makes the MFMA operand
-//     reads (16 consecutive rows, one chunk) hit all 64 LDS banks once;
-//   * fragments of the next 16-wide k-step are read from LDS into a second
-//     register set while the current set feeds the MFMAs.
+// The kernels (plan_gemm() chooses; each has its own comment):
+//   * gemm_256x256_kernel, gemm_256x128_kernel: many rows, two wave groups in
+//     opposite phases;
+//   * gemm_ring_kernel: 64 x 64, 64 x 128 and 128 x 128 tiles, for products
+//     whose weights are streamed;
+//   * few_rows_gemm_kernel: gate/up and q/k/v of up to 4 rows.
+// The tile kernels share their operand path: tiles move HBM/L2 -> LDS with
+// global_load_lds_dwordx4 (no register staging) into stages of 64 K columns,
+// later stages in flight while one is multiplied (vmcnt counts them out, so a
+// barrier never waits for the whole ring).  Each wave-load writes 1 KB = 8
+// tile rows of 128 bytes; the 16-byte chunk index of row r is XOR-ed with
+// (r >> 1) & 7, which makes the MFMA operand reads (16 consecutive rows, one
+// chunk) hit all 64 LDS banks once.
+//
 // Work-groups are dealt round-robin over the 8 XCDs; the tile order is remapped
 // so that the M tiles sharing one weight tile run on one XCD and hit its L2.
 //
@@ -49,10 +42,27 @@ namespace {
 
 constexpr size_t kPartialCap = 64ull << 20;   // bytes of split-K partials (workspace)
 
-typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) char lds_char;
 
-__device__ __forceinline__ void load_lds16(const void* g, void* lds) {
-  __builtin_amdgcn_global_load_lds(g, (lds_void*)lds, 16, 0, 0);
+// Direct global -> LDS load of 16 bytes per lane from base + voff to the
+// wave-uniform LDS address `lds` + 16 * lane.  In assembly, so that the
+// compiler does not wait for it at the next LDS read; the kernels' own vmcnt
+// waits and barriers order it.
+__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
+               : "memory", "m0");
+}
+
+// Barrier that no memory access and no instruction is moved across.
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ void wait_lds() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // 16-byte chunk swizzle of tile row `row` (rows of 128 bytes): 16 consecutive
@@ -65,65 +75,54 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Work-group barrier for the LDS ring: this wave's LDS reads are complete
-// (its slot may be refilled by any wave afterwards), but its direct-to-LDS
-// loads of later stages stay in flight.  __syncthreads() would add a
-// work-group fence, i.e. a wait for every outstanding global load, which
-// would leave only one stage of lookahead however deep the ring.
-__device__ __forceinline__ void ring_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// Virtual columns: every group of 64 is one pair of 32-column blocks, the
+// members of pair `v / 64`: rotary partners (dims j, j + d/2) of one head, or
+// (gate, up) of one feature.  A segment (q, k, v) is a whole number of groups.
+struct QkvColumn {
+  int seg;        // 0 q, 1 k, 2 v
+  int head;       // head of the segment
+  int freq0;      // first rotary frequency (first member's dim) of the group
+};
+__device__ __forceinline__ QkvColumn qkv_group(const GemmArgs& a, int v) {
+  QkvColumn q;
+  q.seg = v < a.n0 ? 0 : (v < a.n0 + a.n1 ? 1 : 2);
+  const int local = (v - (q.seg == 0 ? 0 : (q.seg == 1 ? a.n0 : a.n0 + a.n1))) >> 6, qpd = a.head_dim / 64;
+  q.head = local / qpd;
+  q.freq0 = (local % qpd) * 32;
+  return q;
 }
 
-// Virtual-column mapping.  Column u of an output tile belongs to wave column
-// wn = u / TN, MFMA block nb = (u % TN) / 32, lane column c = u % 32.  For
-// EPI_QKV and EPI_GATE_UP, blocks (2p, 2p+1) of a wave column form pair
-// P = (u % BN) / 64 of the tile: rotary partners (dims j, j + d/2) or
-// (gate, up) of one feature.
-template <int EPI, int BN>
-__device__ __forceinline__ const bf16* weight_row(const GemmArgs& a, int tn, int u) {
-  const int P = u >> 6, blk = (u >> 5) & 1, c = u & 31;
+// Weight row of virtual column v.
+template <int EPI>
+__device__ __forceinline__ const bf16* weight_row(const GemmArgs& a, int v) {
+  const int blk = (v >> 5) & 1, c = v & 31;
   if constexpr (EPI == EPI_QKV) {
-    const int vs = tn * BN;
-    const bf16* base;
-    int local;
-    if (vs < a.n0) { base = a.B0; local = vs; }
-    else if (vs < a.n0 + a.n1) { base = a.B1; local = vs - a.n0; }
-    else { base = a.B2; local = vs - a.n0 - a.n1; }
-    const int hd = a.head_dim, qpd = hd / 64;
-    const int head = P / qpd, dim = (P % qpd) * 32 + blk * (hd / 2) + c;
-    return base + (size_t)(local + head * hd + dim) * a.K;
+    const QkvColumn q = qkv_group(a, v);
+    const bf16* base = q.seg == 0 ? a.B0 : (q.seg == 1 ? a.B1 : a.B2);
+    return base + (size_t)(q.head * a.head_dim + q.freq0 + blk * (a.head_dim / 2) + c) * a.K;
   } else if constexpr (EPI == EPI_GATE_UP) {
-    const int f = tn * (BN / 2) + P * 32 + c;
-    return (blk ? a.B1 : a.B0) + (size_t)f * a.K;
+    return (blk ? a.B1 : a.B0) + (size_t)((v >> 6) * 32 + c) * a.K;
   } else {
-    return a.B0 + (size_t)(tn * BN + u) * a.K;
+    return a.B0 + (size_t)v * a.K;
   }
 }
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
-// Pair epilogues: (x1, x2) are the two members of pair P of tile tn, lane
-// column c, output row `row`.
-template <int BN>
-__device__ __forceinline__ void epi_qkv(const GemmArgs& a, int row, int tn, int P, int c, float x1,
-                                        float x2) {
-  const int vs = tn * BN;
-  int seg, local;
-  if (vs < a.n0) { seg = 0; local = vs; }
-  else if (vs < a.n0 + a.n1) { seg = 1; local = vs - a.n0; }
-  else { seg = 2; local = vs - a.n0 - a.n1; }
-  const int hd = a.head_dim, qpd = hd / 64, half = hd / 2;
-  const int head = local / hd + P / qpd;
-  const int fi = (P % qpd) * 32 + c;           // rotary frequency index = first dim of the pair
-  if (seg < 2) {
+// Pair epilogues of the split-K reduction: (x1, x2) are the two members of the
+// pair of 64-column group g, lane column c, output row `row`.
+__device__ __forceinline__ void epi_qkv(const GemmArgs& a, int row, int g, int c, float x1, float x2) {
+  const QkvColumn q = qkv_group(a, g * 64);
+  const int hd = a.head_dim, half = hd / 2, fi = q.freq0 + c;
+  if (q.seg < 2) {
     const float2 cs = a.rope_cs[(size_t)row * half + fi];
     const float y1 = x1 * cs.x - x2 * cs.y;
     const float y2 = x2 * cs.x + x1 * cs.y;
     x1 = y1;
     x2 = y2;
   }
-  if (seg == 0) {
-    bf16* pq = a.q_out + (size_t)row * a.n0 + head * hd + fi;
+  if (q.seg == 0) {
+    bf16* pq = a.q_out + (size_t)row * a.n0 + q.head * hd + fi;
     pq[0] = (bf16)x1;
     pq[half] = (bf16)x2;
   } else {
@@ -131,17 +130,14 @@ __device__ __forceinline__ void epi_qkv(const GemmArgs& a, int row, int tn, int 
     const SampleInfo s = a.samples[t.sample];
     const int slot = s.seq_len + t.node;
     bf16* pk = a.kv_pool + s.kv_base +
-               ((((size_t)a.layer * 2 + (seg - 1)) * a.n_kv_heads + head) * s.cap + slot) * hd + fi;
+               ((((size_t)a.layer * 2 + (q.seg - 1)) * a.n_kv_heads + q.head) * s.cap + slot) * hd + fi;
     pk[0] = (bf16)x1;
     pk[half] = (bf16)x2;
   }
 }
 
-template <int BN>
-__device__ __forceinline__ void epi_gate_up(const GemmArgs& a, int row, int tn, int P, int c,
-                                            float g, float u) {
-  const int f = tn * (BN / 2) + P * 32 + c;
-  a.act_out[(size_t)row * (a.N / 2) + f] = (bf16)(silu(g) * u);
+__device__ __forceinline__ void epi_gate_up(const GemmArgs& a, int row, int g, int c, float gate, float up) {
+  a.act_out[(size_t)row * (a.N / 2) + g * 32 + c] = (bf16)(silu(gate) * up);
 }
 
 // Work-group b runs on XCD b % 8, which receives q + 1 work-groups (x < r)
@@ -151,325 +147,6 @@ __device__ __forceinline__ void epi_gate_up(const GemmArgs& a, int row, int tn, 
 __device__ __forceinline__ int xcd_contiguous(int b, int total) {
   const int q = total >> 3, r = total & 7, x = b & 7, j = b >> 3;
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
-
-template <int EPI, int BM, int BN, int WM, int NS>
-__global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmArgs a) {
-  constexpr int NW = 4, BK = 64, WN = NW / WM;
-  constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
-  constexpr int ROWB = BK * 2, CPR = BK / 8, RPL = 1024 / ROWB;  // row bytes, chunks, rows per load
-  constexpr int KS = BK / 16;                                     // MFMA k-steps per K step
-  constexpr int A_BYTES = BM * ROWB, STAGE = (BM + BN) * ROWB;
-  constexpr int A_LOADS = A_BYTES / 1024 / NW, B_LOADS = BN * ROWB / 1024 / NW;
-  constexpr int LPW = A_LOADS + B_LOADS;    // wave-loads per wave and stage
-  static_assert(MB >= 1 && NB >= 2 && A_LOADS >= 1 && B_LOADS >= 1, "tile shape");
-  static_assert(A_BYTES % (1024 * NW) == 0 && BN * ROWB % (1024 * NW) == 0, "loads per wave");
-  static_assert(NS >= 2 && (NS - 2) * LPW <= 63, "ring depth (vmcnt holds at most 63)");
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-
-  // The wave index is made scalar so that every LDS destination (M0) of the
-  // direct loads is computed in scalar registers.
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ntm = (a.M + BM - 1) / BM;
-  const int tiles = ntm * (a.N / BN);
-  const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int tile = bid % tiles, split = bid / tiles;
-  const int tm = tile % ntm, tn = tile / ntm;
-  const int KT = a.K / BK / a.ksplit;            // K steps of this split
-  const int k_off = split * KT * BK;
-
-  // Wave-load j of this wave fills tile rows [(wave*LOADS + j)*RPL, +RPL);
-  // lane l lands at row l/CPR, physical chunk l%CPR, so it fetches logical
-  // chunk (l%CPR) ^ swz(row).
-  const int lr = lane / CPR, lc = lane % CPR;
-  const bf16* pa[A_LOADS];
-  const bf16* pb[B_LOADS];
-#pragma unroll
-  for (int j = 0; j < A_LOADS; ++j) {
-    const int trow = (wave * A_LOADS + j) * RPL + lr;
-    int row = tm * BM + trow;
-    row = row < a.M ? row : a.M - 1;      // rows past M repeat the last row; never stored
-    pa[j] = a.A + (size_t)row * a.K + k_off + ((lc ^ swz(trow)) << 3);
-  }
-#pragma unroll
-  for (int j = 0; j < B_LOADS; ++j) {
-    const int trow = (wave * B_LOADS + j) * RPL + lr;
-    pb[j] = weight_row<EPI, BN>(a, tn, trow) + k_off + ((lc ^ swz(trow)) << 3);
-  }
-  // Part q of stage kt's loads (every KS-th wave-load), so that a stage's
-  // loads are spread between the MFMA blocks of a K step instead of issued
-  // in one burst.
-  auto issue_q = [&](int kt, int slot, int q) {
-    char* base = smem + slot * STAGE;
-#pragma unroll
-    for (int j = 0; j < A_LOADS; ++j)
-      if (j % KS == q) load_lds16(pa[j] + kt * BK, base + (wave * A_LOADS + j) * 1024);
-#pragma unroll
-    for (int j = 0; j < B_LOADS; ++j)
-      if (j % KS == q) load_lds16(pb[j] + kt * BK, base + A_BYTES + (wave * B_LOADS + j) * 1024);
-  };
-
-  f32x16 acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x16{};
-
-  const int wm = wave / WN, wn = wave % WN;
-  int arow[MB], brow[NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) arow[i] = wm * TM + i * 32 + (lane & 31);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) brow[j] = wn * TN + j * 32 + (lane & 31);
-
-  bf16x8 fa[2][MB], fb[2][NB];
-  auto load_frags = [&](const char* st, int ks, int set) {
-    const int chunk = ks * 2 + (lane >> 5);
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-      fa[set][i] = *(const bf16x8*)(st + arow[i] * ROWB + ((chunk ^ swz(arow[i])) << 4));
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      fb[set][j] = *(const bf16x8*)(st + A_BYTES + brow[j] * ROWB + ((chunk ^ swz(brow[j])) << 4));
-  };
-  auto mfmas = [&](int set) {
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i], fb[set][j], acc[i][j], 0, 0, 0);
-  };
-
-  // Prologue: stages 0 .. NS-2 in flight, wait for stage 0.
-#pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
-    if (st < KT) {
-#pragma unroll
-      for (int q = 0; q < KS; ++q) issue_q(st, st, q);
-    }
-  if (KT >= NS - 1) wait_vm<(NS - 2) * LPW>();
-  else wait_vm<0>();
-  ring_barrier();
-  // Stage pk (slot ps) is issued part by part between the MFMA blocks of the
-  // current step; -1 when none is left.
-  int pk = NS - 1 < KT ? NS - 1 : -1, ps = NS - 1;
-  if (pk >= 0) issue_q(pk, ps, 0);
-  load_frags(smem, 0, 0);
-  for (int kt = 0; kt < KT; ++kt) {
-    const char* st = smem + (kt % NS) * STAGE;
-#pragma unroll
-    for (int ks = 0; ks + 1 < KS; ++ks) {
-      load_frags(st, ks + 1, (ks + 1) & 1);
-      if (pk >= 0) issue_q(pk, ps, ks + 1);
-      mfmas(ks & 1);
-    }
-    pk = -1;
-    if (kt + 1 < KT) {
-      // Stage kt+1 has landed for every wave (stages kt+2 .. kt+NS-1 may
-      // still be in flight), and every wave is done reading stage kt (its
-      // last fragments are in registers): that slot takes stage kt+NS.
-      if (kt + NS - 1 < KT) wait_vm<(NS - 2) * LPW>();
-      else wait_vm<0>();
-      ring_barrier();
-      if (kt + NS < KT) {
-        pk = kt + NS;
-        ps = kt % NS;
-        issue_q(pk, ps, 0);
-      }
-      load_frags(smem + ((kt + 1) % NS) * STAGE, 0, 0);
-    }
-    mfmas((KS - 1) & 1);
-  }
-
-  // Accumulator layout of a 32x32 block: lane l, element e holds
-  // row 8*(e/4) + 4*(l/32) + e%4, column l%32.
-  const int c = lane & 31;
-  const int rbase = tm * BM + wm * TM + 4 * (lane >> 5);
-
-  if (a.ksplit > 1) {
-    // Raw fp32 tile of this split, virtual column order.
-    float* out = a.partial + (size_t)split * a.M * a.N + tn * BN + wn * TN + c;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          if (row < a.M) out[(size_t)row * a.N + j * 32] = acc[i][j][e];
-        }
-    return;
-  }
-
-  if constexpr (EPI == EPI_RESID) {
-    // Read a whole 32x32 block of the residual before writing any of it, so
-    // the 16 loads per lane are in flight together.
-    float* xcol = a.x + tn * BN + wn * TN + c;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        float xv[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          xv[e] = row < a.M ? xcol[(size_t)row * a.N + j * 32] : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          if (row < a.M) xcol[(size_t)row * a.N + j * 32] = xv[e] + acc[i][j][e];
-        }
-      }
-  } else if constexpr (EPI == EPI_GATE_UP) {
-#pragma unroll
-    for (int p = 0; p < NB / 2; ++p)
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          if (row >= a.M) continue;
-          epi_gate_up<BN>(a, row, tn, wn * (NB / 2) + p, c, acc[i][2 * p][e], acc[i][2 * p + 1][e]);
-        }
-  } else if constexpr (EPI == EPI_QKV) {
-    // The same arithmetic as epi_qkv, with the segment and head taken once
-    // per wave and, for each 32-row block, every row's rotary angles and
-    // destination fetched before any is used, so those loads (and the
-    // token -> sample -> cache slot chain of K and V rows) are in flight
-    // together instead of one row after another.
-    const int vs = tn * BN;
-    const int seg = vs < a.n0 ? 0 : (vs < a.n0 + a.n1 ? 1 : 2);
-    const int local = vs - (seg == 0 ? 0 : (seg == 1 ? a.n0 : a.n0 + a.n1));
-    const int hd = a.head_dim, qpd = hd / 64, half = hd / 2;
-#pragma unroll
-    for (int p = 0; p < NB / 2; ++p) {
-      const int P = wn * (NB / 2) + p;
-      const int head = local / hd + P / qpd;
-      const int fi = (P % qpd) * 32 + c;
-#pragma unroll
-      for (int i = 0; i < MB; ++i) {
-        float2 cs[16];
-        bf16* dst[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          row = row < a.M ? row : a.M - 1;        // loads only; stores are guarded below
-          cs[e] = seg < 2 ? a.rope_cs[(size_t)row * half + fi] : float2{1.f, 0.f};
-        }
-        if (seg == 0) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-            dst[e] = a.q_out + (size_t)row * a.n0 + head * hd + fi;
-          }
-        } else {
-          int smp[16], node[16];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-            row = row < a.M ? row : a.M - 1;
-            smp[e] = a.toks[row].sample;
-            node[e] = a.toks[row].node;
-          }
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const SampleInfo sv = a.samples[smp[e]];
-            dst[e] = a.kv_pool + sv.kv_base +
-                     ((((size_t)a.layer * 2 + (seg - 1)) * a.n_kv_heads + head) * sv.cap + sv.seq_len +
-                      node[e]) * hd + fi;
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          if (row >= a.M) continue;
-          float x1 = acc[i][2 * p][e], x2 = acc[i][2 * p + 1][e];
-          if (seg < 2) {
-            const float y1 = x1 * cs[e].x - x2 * cs[e].y;
-            const float y2 = x2 * cs[e].x + x1 * cs[e].y;
-            x1 = y1;
-            x2 = y2;
-          }
-          dst[e][0] = (bf16)x1;
-          dst[e][half] = (bf16)x2;
-        }
-      }
-    }
-  } else {  // EPI_ARGMAX: one partial (max, lowest index) per row and wave slab of TN columns
-    const int col0 = tn * BN + wn * TN + c;
-    const int parts = a.N / TN;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-        float v = acc[i][0][e];
-        int idx = col0;
-#pragma unroll
-        for (int j = 1; j < NB; ++j)
-          if (acc[i][j][e] > v) { v = acc[i][j][e]; idx = col0 + 32 * j; }
-        if (a.logits != nullptr && row < a.M) {
-#pragma unroll
-          for (int j = 0; j < NB; ++j) a.logits[(size_t)row * a.N + col0 + 32 * j] = acc[i][j][e];
-        }
-#pragma unroll
-        for (int m = 16; m >= 1; m >>= 1) {
-          const float ov = __shfl_xor(v, m);
-          const int oi = __shfl_xor(idx, m);
-          if (ov > v || (ov == v && oi < idx)) { v = ov; idx = oi; }
-        }
-        if (c == 0 && row < a.M) {
-          a.part_val[(size_t)row * parts + tn * WN + wn] = v;
-          a.part_idx[(size_t)row * parts + tn * WN + wn] = idx;
-        }
-      }
-  }
-}
-
-// ---- many rows: 256-row tiles, two wave groups in opposite phases ---------
-//
-// Both kernels below run 8 waves, two per SIMD, as two groups of four (group g
-// = wave / 4; waves w and w + 4 share a SIMD).  A K step is cut into phases,
-// each a memory part (fragment reads from LDS, direct loads of a later K step)
-// and an MFMA part, separated by work-group barriers; group 1 runs one barrier
-// behind group 0, so on every SIMD one wave's MFMAs always meet the other
-// wave's memory part and the matrix core does not wait for LDS.  (In the ring
-// kernel above all waves read, then all multiply.)  Measured on the gate/up
-// product of the 8B shape (28672 x 4096, weights from HBM), us at 512 / 1024 /
-// 4096 rows: ring kernel 150 / 253 / 878, these phases with the same 32x32x16
-// instructions 124 / 232 / 768.  The loop then issues MFMAs in 97 % of its
-// cycles and the card's power limit sets the clock (about 1.4 GHz), so energy
-// per product counts: 16x16x32 instructions, whose accumulator traffic per flop
-// is half, sustain 2.06 against 1.83 PFLOP/s in a loop of MFMAs alone, and take
-// the same product to 106 / 213 / 699 us (1.38 PFLOP/s at 4096 rows).
-//
-// The products are taken as D = W . A^T, so a lane's four accumulators of a
-// 16 x 16 block are four consecutive output columns of one row: acc[i][j][e] =
-// row 16 i + lane % 16, column 16 j + 4 (lane / 16) + e of the wave's tile.
-// Every output goes out as 8 or 16 bytes per lane.
-
-typedef __attribute__((address_space(3))) char lds_char;
-
-// Direct global -> LDS load of 16 bytes per lane from base + voff to the
-// wave-uniform LDS address `lds` + 16 * lane.  In assembly, so that the
-// compiler does not wait for it at the next LDS read; the kernels' own vmcnt
-// waits and barriers order it.
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
-               : "memory", "m0");
-}
-
-// Barrier that no instruction is scheduled across.
-__device__ __forceinline__ void phase_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-__device__ __forceinline__ void wait_lds() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Output tile of logical work-group id `tile`.  Up to 8 M tiles: all M tiles
@@ -491,14 +168,17 @@ __device__ __forceinline__ void tile_at(int tile, int ntm, int ntn, int* tm, int
   *tn = gi * GN + in / rows;
 }
 
-// The epilogues.  The wave's tile starts at row row0 and column col0 (a
-// multiple of 64) of tile (tm, tn); columns j = 0, 1 (mod 4) and their partners
-// j + 2 form the pairs of weight_row().
+// The epilogues.  The products are taken as D = W . A^T, so a lane's four
+// accumulators of a 16 x 16 block are four consecutive output columns of one
+// row: acc[i][j][e] = row 16 i + lane % 16, column 16 j + 4 (lane / 16) + e of
+// the wave's tile, and every output goes out as 8 or 16 bytes per lane.  The
+// wave's tile starts at row row0 and column col0 (a
+// multiple of 64) of tile (tm, tn); blocks j and j + 2 (j = 0, 1) hold the pairs of weight_row().
 template <int EPI, int BM, int BN, int MB, int NB>
 __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tm, int tn,
                                               int row0, int col0, int split, int lane) {
   const int m = tm * BM + row0 + (lane & 15), c4 = 4 * (lane >> 4);
-  if (a.ksplit > 1) {      // raw fp32 tile of this split, virtual column order
+  if (a.plan.splits > 1) {      // raw fp32 tile of this split, virtual column order
     float* out = a.partial + (size_t)split * a.M * a.N + tn * BN + col0 + c4;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
@@ -511,18 +191,19 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
   }
   if constexpr (EPI == EPI_RESID) {
     float* x = a.x + tn * BN + col0 + c4;
+    constexpr int RP = MB < 2 ? 1 : 2;       // rows whose residuals are in flight together
 #pragma unroll
-    for (int i0 = 0; i0 < MB; i0 += 2) {     // two rows' residuals in flight together
-      f32x4 xv[2][NB];
+    for (int i0 = 0; i0 < MB; i0 += RP) {
+      f32x4 xv[RP][NB];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < RP; ++i) {
         const int row = m + 16 * (i0 + i);
         if (row < a.M)
 #pragma unroll
           for (int j = 0; j < NB; ++j) xv[i][j] = *(const f32x4*)(x + (size_t)row * a.N + 16 * j);
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < RP; ++i) {
         const int row = m + 16 * (i0 + i);
         if (row < a.M)
 #pragma unroll
@@ -545,11 +226,8 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
     }
   } else if constexpr (EPI == EPI_QKV) {
     static_assert(NB == 4, "one pair of 32-column blocks per wave");
-    const int vs = tn * BN;
-    const int seg = vs < a.n0 ? 0 : (vs < a.n0 + a.n1 ? 1 : 2);
-    const int local = vs - (seg == 0 ? 0 : (seg == 1 ? a.n0 : a.n0 + a.n1));
-    const int hd = a.head_dim, qpd = hd / 64, half = hd / 2, P = col0 >> 6;
-    const int head = local / hd + P / qpd, fi = (P % qpd) * 32 + c4;
+    const QkvColumn q = qkv_group(a, tn * BN + col0);
+    const int seg = q.seg, head = q.head, hd = a.head_dim, half = hd / 2, fi = q.freq0 + c4;
     // Every row's destination first (for K and V through token -> sample ->
     // cache slot), so that those dependent loads are in flight together.
     bf16* dst[MB];
@@ -632,6 +310,23 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
   }
 }
 
+// ---- many rows: 256-row tiles, two wave groups in opposite phases ---------
+//
+// Both kernels below run 8 waves, two per SIMD, as two groups of four (group g
+// = wave / 4; waves w and w + 4 share a SIMD).  A K step is cut into phases,
+// each a memory part (fragment reads from LDS, direct loads of a later K step)
+// and an MFMA part, separated by work-group barriers; group 1 runs one barrier
+// behind group 0, so on every SIMD one wave's MFMAs always meet the other
+// wave's memory part and the matrix core does not wait for LDS.  (In a plain ring
+// all waves read, then all multiply.)  Measured on the gate/up
+// product of the 8B shape (28672 x 4096, weights from HBM), us at 512 / 1024 /
+// 4096 rows: plain ring 150 / 253 / 878, these phases with the same 32x32x16
+// instructions 124 / 232 / 768.  The loop then issues MFMAs in 97 % of its
+// cycles and the card's power limit sets the clock (about 1.4 GHz), so energy
+// per product counts: 16x16x32 instructions, whose accumulator traffic per flop
+// is half, sustain 2.06 against 1.83 PFLOP/s in a loop of MFMAs alone, and take
+// the same product to 106 / 213 / 699 us (1.38 PFLOP/s at 4096 rows).
+
 // 256 x 256 tiles, 64-wide K steps in two stages of 64 KB.  Group g holds rows
 // 128 g .., wave q = wave % 4 of it columns 64 q ..: 128 x 64 per wave.  Every
 // step is four phases of 16 MFMAs, one quadrant (64 rows x 32 columns, K = 64)
@@ -652,7 +347,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x256_kernel(GemmArgs a) {
   const int split = bid / tiles;
   int tm, tn;
   tile_at(bid % tiles, ntm, ntn, &tm, &tn);
-  const int KT = a.K / 64 / a.ksplit;            // K steps of this split (even)
+  const int KT = a.K / 64 / a.plan.splits;            // K steps of this split (even)
   const size_t k_off = (size_t)split * KT * 64;
 
   // Wave-load j of half hh: 8 tile rows of 128 bytes; lane l lands at row l / 8,
@@ -661,7 +356,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x256_kernel(GemmArgs a) {
   uint32_t va[2][2], vb[2][2], la[2][2], lb[2][2];
   const int mlast = a.M - 1 - tm * BM;           // rows past M repeat the last row; never stored
   const bf16* abase = a.A + (size_t)tm * BM * a.K + k_off;
-  const bf16* bbase[2] = {weight_row<EPI, BN>(a, tn, 0) + k_off, weight_row<EPI, BN>(a, tn, 32) + k_off};
+  const bf16* bbase[2] = {weight_row<EPI>(a, tn * BN) + k_off, weight_row<EPI>(a, tn * BN + 32) + k_off};
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
@@ -669,7 +364,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x256_kernel(GemmArgs a) {
       const int c = wave * 2 + j;
       const int ra = (c >> 3) * 128 + hh * 64 + (c & 7) * 8, rb = (c >> 2) * 64 + hh * 32 + (c & 3) * 8;
       va[hh][j] = (uint32_t)min(ra + lr, mlast) * a.K * 2 + ((lc ^ swz(ra + lr)) << 4);
-      vb[hh][j] = (uint32_t)((const char*)(weight_row<EPI, BN>(a, tn, rb + lr) + k_off) - (const char*)bbase[hh]) +
+      vb[hh][j] = (uint32_t)((const char*)(weight_row<EPI>(a, tn * BN + rb + lr) + k_off) - (const char*)bbase[hh]) +
                   ((lc ^ swz(rb + lr)) << 4);
       la[hh][j] = ra * ROWB;
       lb[hh][j] = BOFF + rb * ROWB;
@@ -792,7 +487,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
   const int split = bid / tiles;
   int tm, tn;
   tile_at(bid % tiles, ntm, ntn, &tm, &tn);
-  const int KT = a.K / 64 / a.ksplit;            // at least 2
+  const int KT = a.K / 64 / a.plan.splits;            // at least 2
   const size_t k_off = (size_t)split * KT * 64;
 
   // Wave-loads as above: wave w loads A rows 32 w .. and weight rows 16 w ..
@@ -801,7 +496,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
   uint32_t va[4], vb[2];
   const int mlast = a.M - 1 - tm * BM;
   const bf16* abase = a.A + (size_t)tm * BM * a.K + k_off;
-  const bf16* bbase = weight_row<EPI, BN>(a, tn, (wave >> 1) * 32) + k_off;
+  const bf16* bbase = weight_row<EPI>(a, tn * BN + (wave >> 1) * 32) + k_off;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int ra = (wave * 4 + j) * 8 + lr;
@@ -810,7 +505,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int rb = (wave * 2 + j) * 8 + lr;
-    vb[j] = (uint32_t)((const char*)(weight_row<EPI, BN>(a, tn, rb) + k_off) - (const char*)bbase) +
+    vb[j] = (uint32_t)((const char*)(weight_row<EPI>(a, tn * BN + rb) + k_off) - (const char*)bbase) +
             ((lc ^ swz(rb)) << 4);
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
@@ -845,9 +540,11 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) fb[j] = *(const bf16x8*)(brows + st + j * 16 * ROWB + ro[ks]);
   };
+  // The reads are complete before the barrier: the other group may refill the
+  // stage right after it.
   auto multiply = [&]() {
-    phase_barrier();
     wait_lds();
+    phase_barrier();
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -884,6 +581,117 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
   epilogue_rows<EPI, BM, BN, 4, 4>(a, acc, tm, tn, wm * 64, wn * 64, split, lane);
 }
 
+// ---- the ring kernel: products whose weights are streamed -------------------
+//
+// BM x BN tiles on 4 waves, each BM / WM x 64 in a WM x BN/64 grid, NS stages.
+// Up to some 256 rows a product is bound by the bytes its CUs can take in: the
+// weights from HBM (about 6 TB/s) and, as often as there are weight tiles, the
+// rows from L2 (about 13 TB/s over the chip), so the tile is chosen for the
+// fewest of both with every CU loading: 64 x 64 while the rows are few (its 64
+// KB leave two work-groups on a CU, each covering the other's waits), then
+// 64 x 128 (72 KB, two) and 128 x 128 (128 KB, one).  Deeper rings, and rings in
+// which some waves load only rows and the others only weights, were no faster.
+// An unsplit product starts its K loop at a step that depends on the weight
+// tile (and wraps around): with all CUs at the same K of rows 2^n bytes apart
+// the loads meet in a few HBM channels (8B gate/up at 64 rows 49.3 -> 43.7 us =
+// 5.4 TB/s of weights, 1B gate/up 17.8 -> 14.8); K splits are spread already.
+// Measured against 32 x 256 and 64 x 256 tiles with 32x32x16 instructions, us
+// with the split-K reduction, 8B shape at 16 / 64 rows: gate/up 47.3 -> 42.7 /
+// 57.4 -> 43.8; down with its norm 30.5 -> 27.4 / 33.3 -> 30.0; O with its norm
+// 15.9 -> 13.3 / 18.6 -> 14.4; q/k/v 16.1 -> 14.1 / 19.3 -> 16.5.
+template <int EPI, int BM, int BN, int NS>
+__global__ __launch_bounds__(256) void gemm_ring_kernel(GemmArgs a) {
+  constexpr int WN = BN / 64, WM = 4 / WN, MB = BM / WM / 16;
+  constexpr int ROWB = 128, STAGE = (BM + BN) * ROWB, BOFF = BM * ROWB;
+  constexpr int AL = BM / 32, BL = BN / 32;      // wave-loads per wave and stage
+  static_assert(MB >= 1 && (NS - 2) * (AL + BL) <= 63, "tile shape");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int ntm = (a.M + BM - 1) / BM, ntn = a.N / BN, tiles = ntm * ntn;
+  const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int split = bid / tiles;
+  int tm, tn;
+  tile_at(bid % tiles, ntm, ntn, &tm, &tn);
+  const int KT = a.K / 64 / a.plan.splits;            // K steps of this split
+  const size_t k_off = (size_t)split * KT * 64;
+
+  // Wave w loads A rows 8 AL w .. and weight rows 8 BL w .. (at most 32, which
+  // lie in one 32-column block, of one weight matrix).
+  const int lr = lane >> 3, lc = lane & 7;
+  uint32_t va[AL], vb[BL];
+  const int mlast = a.M - 1 - tm * BM;           // rows past M repeat the last row; never stored
+  const bf16* abase = a.A + (size_t)tm * BM * a.K + k_off;
+  const bf16* bbase = weight_row<EPI>(a, tn * BN + wave * BL * 8) + k_off;
+#pragma unroll
+  for (int j = 0; j < AL; ++j) {
+    const int ra = (wave * AL + j) * 8 + lr;
+    va[j] = (uint32_t)min(ra, mlast) * a.K * 2 + ((lc ^ swz(ra)) << 4);
+  }
+#pragma unroll
+  for (int j = 0; j < BL; ++j) {
+    const int rb = (wave * BL + j) * 8 + lr;
+    vb[j] = (uint32_t)((const char*)(weight_row<EPI>(a, tn * BN + rb) + k_off) - (const char*)bbase) +
+            ((lc ^ swz(rb)) << 4);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+  const uint32_t lds_a = lds0 + wave * AL * 1024, lds_b = lds0 + BOFF + wave * BL * 1024;
+  const int rot = a.plan.splits == 1 ? tn * 5 % KT : 0;
+  auto load = [&](int kt, uint32_t st) {
+    const int k = kt + rot < KT ? kt + rot : kt + rot - KT;
+    const char* bs = (const char*)bbase + (size_t)k * ROWB;
+    const char* as = (const char*)abase + (size_t)k * ROWB;
+#pragma unroll
+    for (int j = 0; j < BL; ++j) dma16(bs, vb[j], lds_b + st + j * 1024);
+#pragma unroll
+    for (int j = 0; j < AL; ++j) dma16(as, va[j], lds_a + st + j * 1024);
+  };
+
+  f32x4 acc[MB][4];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
+  const int r = lane & 15;
+  uint32_t ro[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) ro[ks] = r * ROWB + (((4 * ks + (lane >> 4)) ^ swz(r)) << 4);
+  const char* arows = smem + wm * (BM / WM) * ROWB;
+  const char* brows = smem + BOFF + wn * 64 * ROWB;
+
+#pragma unroll
+  for (int k = 0; k < NS - 1; ++k)
+    if (k < KT) load(k, k * STAGE);
+  uint32_t st = 0, fill = (NS - 1) * STAGE;      // stage being read, stage being filled
+  for (int kt = 0; kt < KT; ++kt) {
+    // Stage kt has landed for every wave after the barrier (later stages may be
+    // in flight), and every wave's reads of stage kt - 1 are complete (its MFMAs
+    // are issued): that stage is refilled.
+    if (kt + NS - 2 < KT) wait_vm<(NS - 2) * (AL + BL)>();
+    else wait_vm<0>();
+    phase_barrier();
+    if (kt + NS - 1 < KT) load(kt + NS - 1, fill);
+    bf16x8 fa[2][MB], fb[2][4];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) fa[ks][i] = *(const bf16x8*)(arows + st + i * 16 * ROWB + ro[ks]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) fb[ks][j] = *(const bf16x8*)(brows + st + j * 16 * ROWB + ro[ks]);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    st = st == (NS - 1) * STAGE ? 0 : st + STAGE;
+    fill = fill == (NS - 1) * STAGE ? 0 : fill + STAGE;
+  }
+  epilogue_rows<EPI, BM, BN, MB, 4>(a, acc, tm, tn, wm * (BM / WM), wn * 64, split, lane);
+}
+
 // ---- few rows: the product is a stream of the weight rows -----------------
 //
 // One work-group of 4 waves owns one unit of 16 weight rows and splits K into
@@ -894,27 +702,21 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
 // step, and the next step's loads are in flight while the current one is
 // multiplied.  The quarters' 16 x 16 tiles meet in LDS and wave 0 sums them
 // in wave order (a fixed order: bitwise reproducible) and applies the
-// epilogue; no K split leaves the work-group, so no reduction kernel follows
-// (a residual product leaves its RMSNorm to the caller).  Units: QKV = 8
-// rotary pairs (dims j, j + d/2) of one head, GATE_UP = 8 (gate, up)
-// features, RESID = 16 output columns.  Every unit reads all M activation
-// rows, so the activation bytes grow with M against a fixed weight stream;
-// past skinny_max_rows() the tile kernel's 256-row weight tiles win, and the
-// LM head always takes the tile kernel.  Accumulator layout of the 16 x 16
+// epilogue; no K split leaves the work-group, so no reduction kernel follows.
+// Units: QKV = 8 rotary pairs (dims j, j + d/2) of one head, GATE_UP = 8
+// (gate, up) features.  Every unit reads all M activation rows, so the
+// activation bytes grow with M against a fixed weight stream.  Whole steps of 8
+// layers, with these two products here or on tiles: 8B at 4 rows 1105 or 1108
+// us, at 8 rows 1189 or 1117.  The residual products do not come here, as a K
+// split's reduction takes their RMSNorm with it (one row, with the norm: down
+// 28.7 on tiles, 30.8 here, O 13.4 and 14.7; the 1B step of 8 layers 520 and 550).  Accumulator layout of the 16 x 16
 // block: lane l, element i holds activation row 4 (l / 16) + i and unit row
 // l % 16.
-constexpr int kSkinnyRows = 16;
-// Rows up to which a product takes this path (measured on the 8B shape
-// against the tile kernel with its K splits): q/k/v and gate/up up to 4 rows
-// (at 8 rows the activation re-reads already cost more than the saved
-// reductions); the residual products up to 8 (at 16 rows the RMSNorm that
-// then runs on its own costs more than the fused split-K reduction it
-// replaces).
-template <int EPI>
-constexpr int skinny_max_rows() { return EPI == EPI_RESID ? 8 : 4; }
+constexpr int kUnitRows = 16;
+constexpr int kFewRows = 4;          // activation rows up to which a product comes here
 
 template <int EPI>
-__device__ __forceinline__ const bf16* skinny_row(const GemmArgs& a, int unit, int c) {
+__device__ __forceinline__ const bf16* unit_row(const GemmArgs& a, int unit, int c) {
   if constexpr (EPI == EPI_QKV) {
     const int hd = a.head_dim, upd = hd / 16;       // units per head
     const int head_all = unit / upd, jb = unit % upd;
@@ -926,24 +728,22 @@ __device__ __forceinline__ const bf16* skinny_row(const GemmArgs& a, int unit, i
     else { base = a.B2; head = head_all - nh0 - nh1; }
     const int dim = c < 8 ? jb * 8 + c : hd / 2 + jb * 8 + (c - 8);
     return base + (size_t)(head * hd + dim) * a.K;
-  } else if constexpr (EPI == EPI_GATE_UP) {
+  } else {
     const int f = unit * 8 + (c & 7);
     return (c < 8 ? a.B0 : a.B1) + (size_t)f * a.K;
-  } else {
-    return a.B0 + (size_t)(unit * kSkinnyRows + c) * a.K;
   }
 }
 
 template <int EPI>
-__global__ __launch_bounds__(256) void skinny_gemm_kernel(GemmArgs a) {
-  static_assert(EPI != EPI_ARGMAX, "the LM head streams its rows through the tile kernel");
+__global__ __launch_bounds__(256) void few_rows_gemm_kernel(GemmArgs a) {
+  static_assert(EPI == EPI_QKV || EPI == EPI_GATE_UP, "a product of pairs");
   __shared__ f32x4 red[4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, kq = lane >> 4;
   const int unit = blockIdx.x;
   const int kw = a.K / 4;                            // K of this wave (a multiple of 32)
   const int k0 = wave * kw, k1 = k0 + kw;
-  const bf16* wrow = skinny_row<EPI>(a, unit, c) + kq * 8;
+  const bf16* wrow = unit_row<EPI>(a, unit, c) + kq * 8;
   const bool arow_ok = c < a.M;
   const bf16* arow = a.A + (size_t)(arow_ok ? c : 0) * a.K + kq * 8;
 
@@ -980,13 +780,7 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(GemmArgs a) {
     f32x4 t = red[0][lane];
 #pragma unroll
     for (int w = 1; w < 4; ++w) t += red[w][lane];
-    if constexpr (EPI == EPI_RESID) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + i;
-        if (m < a.M) a.x[(size_t)m * a.N + unit * kSkinnyRows + c] += t[i];
-      }
-    } else if constexpr (EPI == EPI_GATE_UP) {
+    if constexpr (EPI == EPI_GATE_UP) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float u = __shfl_xor(t[i], 8);         // lanes c and c + 8: gate and up of one feature
@@ -1026,20 +820,16 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(GemmArgs a) {
 }
 
 template <int EPI>
-hipError_t launch_skinny(const GemmArgs& a, hipStream_t s) {
-  long grid;
-  if constexpr (EPI == EPI_QKV) grid = (long)(a.n0 + a.n1 + a.n2) / kSkinnyRows;
-  else grid = (long)a.N / kSkinnyRows;
-  if (a.norm_done) *a.norm_done = false;
-  skinny_gemm_kernel<EPI><<<(unsigned)grid, 256, 0, s>>>(a);
+hipError_t launch_few_rows(const GemmArgs& a, hipStream_t s) {
+  const long grid = (long)a.N / kUnitRows;
+  few_rows_gemm_kernel<EPI><<<(unsigned)grid, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
 // Sum the K splits in split order and apply the epilogue.  Thread (row,
 // group g of 64 virtual columns, lane column c) owns virtual columns g*64 + c
-// and g*64 + 32 + c: pair (g % (BN/64)) of tile g / (BN/64), or two residual
-// columns.
-template <int EPI, int BN>
+// and g*64 + 32 + c: a pair, or two residual columns.
+template <int EPI>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   const int half_n = a.N / 2;
@@ -1048,18 +838,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a) {
   const int g = rem >> 5, c = rem & 31;
   const size_t base = (size_t)row * a.N + g * 64 + c;
   float x1 = 0.f, x2 = 0.f;
-  for (int s = 0; s < a.ksplit; ++s) {
+  for (int s = 0; s < a.plan.splits; ++s) {
     x1 += a.partial[(size_t)s * a.M * a.N + base];
     x2 += a.partial[(size_t)s * a.M * a.N + base + 32];
   }
-  constexpr int PPT = BN / 64;     // pairs per tile
   if constexpr (EPI == EPI_RESID) {
     a.x[base] += x1;
     a.x[base + 32] += x2;
   } else if constexpr (EPI == EPI_QKV) {
-    epi_qkv<BN>(a, row, g / PPT, g % PPT, c, x1, x2);
+    epi_qkv(a, row, g, c, x1, x2);
   } else if constexpr (EPI == EPI_GATE_UP) {
-    epi_gate_up<BN>(a, row, g / PPT, g % PPT, c, x1, x2);
+    epi_gate_up(a, row, g, c, x1, x2);
   }
 }
 
@@ -1089,7 +878,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_norm_kernel(GemmArgs a) {
   }
   int s = 0;
   if constexpr (EAGER && CPT <= 4) {  // eight splits per round while the registers allow
-    for (; s + 8 <= a.ksplit; s += 8) {
+    for (; s + 8 <= a.plan.splits; s += 8) {
       f32x4 p[8][CPT];
 #pragma unroll
       for (int q = 0; q < 8; ++q)
@@ -1104,7 +893,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_norm_kernel(GemmArgs a) {
         for (int k = 0; k < CPT; ++k) t[k] += p[q][k];
     }
   }
-  for (; s + 4 <= a.ksplit; s += 4) {
+  for (; s + 4 <= a.plan.splits; s += 4) {
     f32x4 p[4][CPT];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -1118,7 +907,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_norm_kernel(GemmArgs a) {
 #pragma unroll
       for (int k = 0; k < CPT; ++k) t[k] += p[q][k];
   }
-  for (; s < a.ksplit; ++s)
+  for (; s < a.plan.splits; ++s)
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int c = (threadIdx.x + 256 * k) * 4;
@@ -1170,85 +959,14 @@ bool launch_reduce_norm(const GemmArgs& a, hipStream_t s) {
   }
 }
 
-enum TileShape { TILE_256x256, TILE_256x128, TILE_128x128, TILE_64x256, TILE_32x256 };
-
-struct TilePlan {
-  TileShape shape;
-  int splits;       // K splits
-};
-
-// K splits of the ring kernel's tiles: about one work-group per CU for
-// 128 x 128 (its ring holds a CU's LDS) and two for the skinny ones, at least
-// 8 K steps per split, the splits dividing the K steps, partials within the
-// workspace area.
-int ring_splits(int epi, int BM, long tiles, int M, int N, int K) {
-  if (epi == EPI_ARGMAX) return 1;
-  const long target = BM <= 64 ? 512 : 256;
-  int s = (int)std::max<long>(1, std::min<long>(16, target / tiles));
-  const int kt = K / 64;
-  while (s > 1 && (kt % s != 0 || kt / s < 8 || (size_t)s * M * N * 4 > kPartialCap)) --s;
-  return s;
-}
-
-// Shape and splits (measured over the verify step's products):
-//   * few rows: 32- or 64-row tiles that stream 256 weight rows each;
-//   * up to 128 rows, and products too narrow to give 64 256 x 128 tiles over a
-//     short K: 128 x 128 tiles with split K;
-//   * many rows: 256 x 256 or 256 x 128 tiles, unsplit or with K split, whichever
-//     the cost model below puts first.
-// 256-wide tiles need every weight segment (q/k/v) to be a multiple of 256 so
-// no tile straddles two; 128-wide ones need multiples of 128.
-//
-// The model, in us: rounds of 256 work-groups, each (K steps x step + fixed),
-// plus a reduction that writes and reads the fp32 partials.  The step times are
-// those of a full chip (gate/up, 8B shape: 256 x 256 at 1024 rows 213 us over
-// 2 x 64 steps, 256 x 128 at 4096 rows 824 us over 14 x 64).  Measured us
-// against the form that is not taken, 8B shape, reduction included:
-//   1024 rows: down 256x256 split 4 118, 256x128 split 2 125; O 256x128 split 2
-//   50, 256x256 split 4 53; q/k/v 256x128 64, 256x256 split 2 76;
-//   512 rows: gate/up 256x256 106, 256x128 121; down 256x128 split 4 70,
-//   256x256 split 4 88; O 256x128 split 4 32, split 2 39;
-//   200 rows: gate/up 256x128 65, 256x256 80.
-TilePlan pick_tile(int epi, int M, int N, int K, int n0, int n1, bool may_split) {
-  const bool w256 = N % 256 == 0 && n0 % 256 == 0 && n1 % 256 == 0;
-  auto ring = [&](TileShape t, int BM, int BN) {
-    const long tiles = (long)((M + BM - 1) / BM) * (N / BN);
-    return TilePlan{t, may_split ? ring_splits(epi, BM, tiles, M, N, K) : 1};
-  };
-  if (w256 && M <= 32) return ring(TILE_32x256, 32, 256);
-  if (w256 && M <= 64) return ring(TILE_64x256, 64, 256);
-  const long mt = (M + 255) / 256;
-  if (M <= 128 || (mt * (N / 128) < 64 && K <= 4096)) return ring(TILE_128x128, 128, 128);
-  const int kt = K / 64;
-  TilePlan best{TILE_256x128, 1};
-  double best_us = 1e30;
-  for (const TileShape t : {TILE_256x256, TILE_256x128}) {
-    if (t == TILE_256x256 && !w256) continue;
-    const long tiles = mt * (N / (t == TILE_256x256 ? 256 : 128));
-    const double step = t == TILE_256x256 ? 1.55 : 0.95;
-    for (int s = 1; s <= (may_split && epi != EPI_ARGMAX ? 16 : 1); ++s) {
-      if (s > 1 && (kt % s != 0 || kt / s < 8 || (size_t)s * M * N * 4 > kPartialCap)) continue;
-      if (t == TILE_256x256 && (kt / s) % 2 != 0) continue;     // its steps go in pairs
-      const double rounds = (double)((tiles * s + 255) / 256);
-      double us = rounds * (kt / s * step + 5.0);
-      if (s > 1) us += 4.0 + 8.0 * s * M * N / 4.5e6;
-      if (us < best_us) {
-        best_us = us;
-        best = TilePlan{t, s};
-      }
-    }
-  }
-  return best;
-}
-
-// Sum the splits and apply the epilogue of a product on BN-wide tiles.
-template <int EPI, int BN>
+// Sum the splits and apply the epilogue.
+template <int EPI>
 hipError_t launch_reduce(const GemmArgs& a, hipStream_t s) {
   if (EPI == EPI_RESID && a.norm_out != nullptr && a.N % 4 == 0 && launch_reduce_norm(a, s)) {
     if (a.norm_done) *a.norm_done = true;
   } else {
     const size_t threads = (size_t)a.M * (a.N / 2);
-    splitk_reduce_kernel<EPI, BN><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(a);
+    splitk_reduce_kernel<EPI><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(a);
   }
   return hipGetLastError();
 }
@@ -1263,41 +981,93 @@ hipError_t launch_tiles(Kernel kernel, const GemmArgs& a, hipStream_t s) {
     configured = true;
   }
   const long tiles = (long)((a.M + BM - 1) / BM) * (a.N / BN);
-  kernel<<<(unsigned)(tiles * a.ksplit), THREADS, SMEM, s>>>(a);
-  return a.ksplit > 1 ? launch_reduce<EPI, BN>(a, s) : hipGetLastError();
+  kernel<<<(unsigned)(tiles * a.plan.splits), THREADS, SMEM, s>>>(a);
+  return a.plan.splits > 1 ? launch_reduce<EPI>(a, s) : hipGetLastError();
 }
 
-template <int EPI, int BM, int BN, int WM, int NS>
+template <int EPI, int BM, int BN, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t s) {
-  return launch_tiles<EPI, BM, BN, 256, NS * (BM + BN) * 128>(gemm_ring_kernel<EPI, BM, BN, WM, NS>, a, s);
+  return launch_tiles<EPI, BM, BN, 256, NS * (BM + BN) * 128>(gemm_ring_kernel<EPI, BM, BN, NS>, a, s);
 }
 
 template <int EPI>
-hipError_t launch_epi(GemmArgs a, hipStream_t s) {
-  // Few rows: every supported shape has K a multiple of 128 and head_dim 64
-  // or 128, which the weight-row units assume.
-  if constexpr (EPI != EPI_ARGMAX)
-    if (a.M <= skinny_max_rows<EPI>() && a.K % 128 == 0) return launch_skinny<EPI>(a, s);
-  const TilePlan p = pick_tile(EPI, a.M, a.N, a.K, a.n0, a.n1, a.partial != nullptr);
-  a.ksplit = p.splits;
-  switch (p.shape) {
-    case TILE_256x256:
+hipError_t launch_epi(const GemmArgs& a, hipStream_t s) {
+  if constexpr (EPI == EPI_QKV || EPI == EPI_GATE_UP)
+    if (a.plan.shape == GEMM_FEW_ROWS) return launch_few_rows<EPI>(a, s);
+  switch (a.plan.shape) {
+    case GEMM_256x256:
       return launch_tiles<EPI, 256, 256, 512, 2 * 512 * 128>(gemm_256x256_kernel<EPI>, a, s);
-    case TILE_256x128:
+    case GEMM_256x128:
       return launch_tiles<EPI, 256, 128, 512, 3 * 384 * 128>(gemm_256x128_kernel<EPI>, a, s);
-    case TILE_32x256: return launch_ring<EPI, 32, 256, 1, 3>(a, s);
-    case TILE_64x256: return launch_ring<EPI, 64, 256, 2, 3>(a, s);
-    default: return launch_ring<EPI, 128, 128, 2, 4>(a, s);
+    case GEMM_128x128: return launch_ring<EPI, 128, 128, 4>(a, s);
+    case GEMM_64x128: return launch_ring<EPI, 64, 128, 3>(a, s);
+    case GEMM_64x64: return launch_ring<EPI, 64, 64, 4>(a, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-int gemm_parts(int N, int M, int K) {
-  switch (pick_tile(EPI_ARGMAX, M, N, K, N, 0, false).shape) {
-    case TILE_64x256: return N / 128;
-    default: return N / 64;       // all others: wave slabs of 64 columns
+// The cost model, in us: the larger of the weight stream (6.1 TB/s) and of the
+// work-groups' own time, an eighth of the smaller, which overlaps imperfectly,
+// and for a split the reduction (3.3 + 0.1 per split + its fp32 partials, written
+// and read, at 6 TB/s).  A work-group's K step of 64 takes `step` with the chip
+// full; the 64-row tiles run two to a CU, whose pair takes `pair` steps, and the
+// others' step shrinks to `alone` of it when few CUs work (less L2 traffic, and a
+// higher clock).  `fixed` is each round's prologue and epilogue.  An unsplit
+// residual product leaves its RMSNorm to a launch of its own (5 us); a reduction
+// takes it along.  Fitted to 1381 measurements of the five tiles and their splits
+// on the 8B and 1B shapes' products at 1 to 4096 rows, weights from HBM: 3.4 %
+// rms, and the choice is on average 0.5 % slower than the best one measured.
+GemmPlan plan_gemm(int epi, int M, int N, int K, int n0, int n1, bool norm) {
+  if ((epi == EPI_QKV || epi == EPI_GATE_UP) && M <= kFewRows) return GemmPlan{GEMM_FEW_ROWS, 1};
+  struct Tile {
+    GemmShape shape;
+    int bm, bn;
+    double step, pair, alone, fixed;
+  };
+  static constexpr Tile tiles[] = {{GEMM_256x256, 256, 256, 1.319, 0, 0.705, 3.17},
+                                   {GEMM_256x128, 256, 128, 0.822, 0, 0.769, 2.06},
+                                   {GEMM_128x128, 128, 128, 0.626, 0, 0.854, 1.45},
+                                   {GEMM_64x128, 64, 128, 0.449, 1.607, 1, 0.39},
+                                   {GEMM_64x64, 64, 64, 0.281, 1.776, 1, 0.25}};
+  const int kt = K / 64;
+  const double stream = 2e-6 * N * K / 6.1;
+  GemmPlan best{GEMM_128x128, 1};
+  double best_us = 1e30;
+  for (const Tile& t : tiles) {
+    // A 256-wide tile addresses its weight rows from one base per block parity,
+    // so it needs segments (q/k/v) that are multiples of 256; its K steps go in
+    // pairs.  Every supported width is a multiple of 128.
+    if (t.bn == 256 && (N % 256 || n0 % 256 || n1 % 256)) continue;
+    const long count = (long)((M + t.bm - 1) / t.bm) * (N / t.bn);
+    for (int s = 1; s <= (epi == EPI_ARGMAX ? 1 : 16); ++s) {
+      if (s > 1 && (kt % s != 0 || kt / s < 4 || (size_t)s * M * N * 4 > kPartialCap)) continue;
+      if (t.bn == 256 && (kt / s) % 2 != 0) continue;
+      const long wgs = count * s;
+      const int per = t.pair > 0 ? 512 : 256;            // work-groups of a round
+      const double full = t.pair > 0 ? t.pair : 1;       // steps a full round takes
+      double rounds, steps;
+      if (wgs > 1536) {
+        rounds = (double)wgs / per;
+        steps = rounds * full;
+      } else {
+        const long rest = wgs % per;
+        rounds = (double)((wgs + per - 1) / per);
+        steps = wgs / per * full + (rest > 256 ? full : rest > 0 ? 1 : 0);
+      }
+      const double step = t.step * (t.alone + (1 - t.alone) * std::min(1.0, wgs / 256.0));
+      const double work = kt / s * step * steps + rounds * t.fixed;
+      double us = std::max(stream, work) + 0.13 * std::min(stream, work);
+      if (s > 1) us += 3.3 + 0.1 * s + 8e-6 * s * M * N / 6;
+      else if (norm) us += 5.0;
+      if (us < best_us) {
+        best_us = us;
+        best = GemmPlan{t.shape, s};
+      }
+    }
   }
+  return best;
 }
 
 size_t gemm_partial_bytes() { return kPartialCap; }

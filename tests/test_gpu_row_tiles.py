@@ -50,3 +50,16 @@ def test_row_tiles(cfg, sizes):
     out, r, exc = full_check(cfg, W_cpu, ver, ids, trees, lens, envelope=cfg is LONG)
     check_tree_kv(cfg, ver, ids, trees, lens, r, ids)
     release(ver, W_dev)
+
+
+@pytest.mark.parametrize("cfg,sizes", [
+    (WIDE, [5]),              # few rows on 64 x 64 tiles, q/k/v and gate/up unsplit or split
+    (WIDE, [64]),
+    (WIDE, [40, 25]),         # one row past a 64-row tile
+    (WIDE, [64, 65]),         # one row past 128
+    (LONG, [3, 2]),           # residual products split over K at 5 rows, K = 2048 and 8192
+    (LONG, [65]),
+    (LONG, [128]),
+], ids=["5", "64", "65", "129", "5-long", "65-long", "128-long"])
+def test_ring_tiles(cfg, sizes):
+    test_row_tiles(cfg, sizes)
