@@ -535,8 +535,9 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
 
   // ---- the step ----
   HIP_TRY(launch_tree_meta(d_si, batch, d_par, d_toks, d_anc, D.depth, D.pos, D.anc, s), "tree meta");
-  HIP_TRY(launch_rope_table(d_toks, N, hd, cfg->rope_theta, d_rope, s), "rope table");
-  HIP_TRY(launch_embed(d_tok, (const bf16*)w->tok_embed, d_x, N, H, s), "embed");
+  HIP_TRY(launch_row_front(d_toks, d_tok, (const bf16*)w->tok_embed, (const bf16*)w->attn_norm[0], d_x, d_h,
+                           N, H, cfg->rms_eps, hd, cfg->rope_theta, d_rope, s),
+          "row front");
 
   GemmArgs ga{};
   ga.M = N;
@@ -581,7 +582,6 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     if (!fused) HIP_TRY(launch_rmsnorm(d_x, (const bf16*)gain, d_h, N, H, cfg->rms_eps, s), "rmsnorm");
     return SPEC_OK;
   };
-  HIP_TRY(launch_rmsnorm(d_x, (const bf16*)w->attn_norm[0], d_h, N, H, cfg->rms_eps, s), "rmsnorm");
   const GemmPlan p_qkv = plan_gemm(EPI_QKV, N, (nq + 2 * nkv) * hd, H, nq * hd, nkv * hd, false);
   const GemmPlan p_o = plan_gemm(EPI_RESID, N, H, nq * hd, H, 0, true);
   const GemmPlan p_gate_up = plan_gemm(EPI_GATE_UP, N, 2 * F, H, F, F, false);
@@ -653,16 +653,11 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
                                           accepted_nodes, s);
             }),
             "sampled accept");
-  } else if (samp && samp->eos_token >= 0) {
-    HIP_TRY(timed(SPEC_K_ACCEPT, s, [&] {
-              return launch_accept_eos(d_si, batch, d_tok, d_par, d_toks, d_arg, samp->eos_token,
-                                       accepted_len, next_token, accepted_nodes, s);
-            }),
-            "accept");
   } else {
     HIP_TRY(timed(SPEC_K_ACCEPT, s, [&] {
-              return launch_accept(d_si, batch, d_tok, d_par, d_toks, d_arg, accepted_len,
-                                   next_token, accepted_nodes, s);
+              return launch_accept(d_si, batch, d_tok, d_par, d_toks, d_anc, d_arg,
+                                   samp ? samp->eos_token : -1, accepted_len, next_token, accepted_nodes,
+                                   s);
             }),
             "accept");
   }

@@ -34,15 +34,6 @@ struct NodeSet {
     const int k = t >> 6;
     return k == 0 ? w0 : k == 1 ? w1 : k == 2 ? w2 : w3;
   }
-  __device__ __forceinline__ bool has(int t) const { return (word(t) >> (t & 63)) & 1ull; }
-  __device__ __forceinline__ void add(int t) {
-    const int k = t >> 6;
-    const uint64_t bit = 1ull << (t & 63);
-    w0 |= k == 0 ? bit : 0ull;
-    w1 |= k == 1 ? bit : 0ull;
-    w2 |= k == 2 ? bit : 0ull;
-    w3 |= k == 3 ? bit : 0ull;
-  }
 };
 static_assert(kAncWords == 4, "NodeSet holds four words");
 constexpr int kWave = 64;
@@ -177,18 +168,19 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
 hipError_t launch_tree_meta(const SampleInfo* samples, int batch, const int32_t* parents,
                             TokInfo* toks, uint64_t* anc, int32_t* dbg_depth, int32_t* dbg_pos,
                             uint64_t* dbg_anc, hipStream_t s);
-hipError_t launch_rope_table(const TokInfo* toks, int n, int head_dim, float theta, float2* cs,
-                             hipStream_t s);
-hipError_t launch_embed(const int32_t* tokens, const bf16* table, float* x, int n, int hidden,
-                        hipStream_t s);
+// Rotary angles, embedding (into x) and the first RMSNorm (into out) of n rows.
+hipError_t launch_row_front(const TokInfo* toks, const int32_t* tokens, const bf16* table,
+                            const bf16* gain, float* x, bf16* out, int n, int hidden, float eps,
+                            int head_dim, float theta, float2* cs, hipStream_t s);
 hipError_t launch_rmsnorm(const float* x, const bf16* gain, bf16* out, int n, int hidden,
                           float eps, hipStream_t s);
 hipError_t launch_argmax_reduce(const float* part_val, const int32_t* part_idx, int n, int parts,
                                 int32_t* argmax, int32_t* dbg_argmax, hipStream_t s);
+// Greedy acceptance; eos: the end-of-sequence token, -1 for none.
 hipError_t launch_accept(const SampleInfo* samples, int batch, const int32_t* tokens,
-                         const int32_t* parents, const TokInfo* toks, const int32_t* argmax,
-                         int32_t* accepted_len, int32_t* next_token, int32_t* accepted_nodes,
-                         hipStream_t s);
+                         const int32_t* parents, const TokInfo* toks, const uint64_t* anc,
+                         const int32_t* argmax, int eos, int32_t* accepted_len, int32_t* next_token,
+                         int32_t* accepted_nodes, hipStream_t s);
 // Work-groups one (layer, K/V, kv head) run of `count` tokens takes.
 int64_t kv_transfer_chunks(int count, int head_dim);
 // Copy the runs described by info[0..n) between the pool and the transfer
@@ -208,11 +200,6 @@ hipError_t launch_sample_accept(const SampleInfo* samples, int batch, int n_toke
                                 const float* draft_probs, const float* uniforms, int vocab,
                                 float temperature, int eos, void* scratch, int32_t* accepted_len,
                                 int32_t* next_token, int32_t* accepted_nodes, hipStream_t s);
-// Greedy acceptance with an end-of-sequence token.
-hipError_t launch_accept_eos(const SampleInfo* samples, int batch, const int32_t* tokens,
-                             const int32_t* parents, const TokInfo* toks, const int32_t* argmax,
-                             int eos, int32_t* accepted_len, int32_t* next_token,
-                             int32_t* accepted_nodes, hipStream_t s);
 hipError_t launch_compact(const SampleInfo* samples, int batch, bf16* kv_pool, int n_layers,
                           int n_kv_heads, int head_dim, const int32_t* accepted_len,
                           const int32_t* accepted_nodes, int32_t* new_seq_lens, hipStream_t s);

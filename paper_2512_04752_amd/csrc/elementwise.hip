@@ -1,7 +1,9 @@
-// The small kernels of the verify step: tree metadata, rotary angle table,
-// embedding gather, RMSNorm, the final argmax reduction, greedy tree
-// acceptance and KV compaction.
+// The small kernels of the verify step: tree metadata, what a row needs before
+// the first layer (rotary angles, embedding, first RMSNorm), RMSNorm, the final
+// argmax reduction, greedy tree acceptance and KV compaction.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -55,51 +57,46 @@ __global__ __launch_bounds__(kMaxTree) void tree_meta_kernel(const SampleInfo* s
   if (dbg_pos) dbg_pos[row] = s.seq_len + depth;
 }
 
-// cos/sin of position * theta^(-2j/d), angles in double precision.
-__global__ void rope_table_kernel(const TokInfo* toks, int n, int half, int head_dim, double theta,
-                                  float2* cs) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * half) return;
-  const int row = idx / half, j = idx % half;
-  const double freq = pow(theta, -2.0 * (double)j / (double)head_dim);
-  const double ang = (double)toks[row].pos * freq;
-  double sn, cn;
-  sincos(ang, &sn, &cn);
-  cs[idx] = make_float2((float)cn, (float)sn);
-}
-
-__global__ void embed_kernel(const int32_t* tokens, const bf16* table, float* x, int hidden) {
-  const int row = blockIdx.x;
-  const bf16* src = table + (size_t)tokens[row] * hidden;
-  float* dst = x + (size_t)row * hidden;
-  for (int c = threadIdx.x * 8; c < hidden; c += blockDim.x * 8) {
-    const bf16x8 v = *(const bf16x8*)(src + c);
-    f32x4 lo = {(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-    f32x4 hi = {(float)v[4], (float)v[5], (float)v[6], (float)v[7]};
-    *(f32x4*)(dst + c) = lo;
-    *(f32x4*)(dst + c + 4) = hi;
-  }
-}
-
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
   return v;
 }
 
+// Sum of `ss` over a 256-thread block: the lanes, then the four waves in order.
+__device__ __forceinline__ float block_sum(float ss, float* red) {
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  return red[0] + red[1] + red[2] + red[3];
+}
+
+// Where a row to be normalised comes from: the residual stream, or the
+// embedding table, whose row is then also written to the residual stream.
+struct ResidualRow {
+  const float* x;
+  __device__ __forceinline__ f32x4 load(int c) const { return *(const f32x4*)(x + c); }
+};
+struct EmbeddedRow {
+  const bf16* table;
+  float* x;
+  __device__ __forceinline__ f32x4 load(int c) const {
+    const bf16x4 e = *(const bf16x4*)(table + c);
+    const f32x4 v = {(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
+    *(f32x4*)(x + c) = v;
+    return v;
+  }
+};
+
 // out = bf16(x / sqrt(mean(x^2) + eps) * gain), one 256-thread block per row.
-// CPT > 0: the row is CPT 4-float chunks per thread (hidden <= 1024 * CPT),
+// CPT > 0: the row is CPT 4-element chunks per thread (hidden <= 1024 * CPT),
 // all loaded (with their gains) before any is used, so a short row costs one
 // memory round trip (with few rows there are few blocks to hide latency);
 // CPT = 0: any length, a strided loop.  Both sum each thread's chunks in
 // column order, then the lanes, then the four waves: the same result.
-template <int CPT>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const bf16* gain, bf16* out,
-                                                      int hidden, float eps) {
-  __shared__ float red[4];
-  const int row = blockIdx.x;
-  const float* xr = x + (size_t)row * hidden;
-  bf16* orow = out + (size_t)row * hidden;
+template <int CPT, class Row>
+__device__ __forceinline__ void normalise_row(const Row& row, const bf16* gain, bf16* orow, int hidden,
+                                              float eps, float* red) {
   float ss = 0.f;
   if constexpr (CPT > 0) {
     f32x4 v[CPT];
@@ -108,7 +105,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const bf16
     for (int k = 0; k < CPT; ++k) {
       const int c = (threadIdx.x + 256 * k) * 4;
       if (c < hidden) {
-        v[k] = *(const f32x4*)(xr + c);
+        v[k] = row.load(c);
         g[k] = *(const bf16x4*)(gain + c);
       }
     }
@@ -116,11 +113,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const bf16
     for (int k = 0; k < CPT; ++k)
       if ((threadIdx.x + 256 * k) * 4 < hidden)
         ss += v[k][0] * v[k][0] + v[k][1] * v[k][1] + v[k][2] * v[k][2] + v[k][3] * v[k][3];
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    const float tot = red[0] + red[1] + red[2] + red[3];
-    const float rstd = rsqrtf(tot / (float)hidden + eps);
+    const float rstd = rsqrtf(block_sum(ss, red) / (float)hidden + eps);
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int c = (threadIdx.x + 256 * k) * 4;
@@ -133,22 +126,51 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const bf16
     }
   } else {
     for (int c = threadIdx.x * 4; c < hidden; c += 256 * 4) {
-      const f32x4 v = *(const f32x4*)(xr + c);
+      const f32x4 v = row.load(c);
       ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
     }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    const float tot = red[0] + red[1] + red[2] + red[3];
-    const float rstd = rsqrtf(tot / (float)hidden + eps);
+    const float rstd = rsqrtf(block_sum(ss, red) / (float)hidden + eps);
     for (int c = threadIdx.x * 4; c < hidden; c += 256 * 4) {
-      const f32x4 v = *(const f32x4*)(xr + c);
+      const f32x4 v = row.load(c);
       const bf16x4 g = *(const bf16x4*)(gain + c);
       bf16x4 y;
 #pragma unroll
       for (int k = 0; k < 4; ++k) y[k] = (bf16)(v[k] * rstd * (float)g[k]);
       *(bf16x4*)(orow + c) = y;
     }
+  }
+}
+
+template <int CPT>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const bf16* gain, bf16* out,
+                                                      int hidden, float eps) {
+  __shared__ float red[4];
+  const size_t at = (size_t)blockIdx.x * hidden;
+  normalise_row<CPT>(ResidualRow{x + at}, gain, out + at, hidden, eps, red);
+}
+
+// Everything a row needs before the first layer, one block per row: cos/sin of
+// position * theta^(-2j/d) (angles in double precision), the embedding into the
+// residual stream, and its RMSNorm.  In launches of their own the three took
+// 2.2 + 2.2 + 2.6 us at 16 rows of 256 columns and 4.8 + 24.5 + 16.3 at 4096
+// rows of 4096 (a launch costs about 2 us whatever it does).
+template <int CPT>
+__global__ __launch_bounds__(256) void row_front_kernel(const TokInfo* toks, const int32_t* tokens,
+                                                        const bf16* table, const bf16* gain, float* x,
+                                                        bf16* out, int hidden, float eps, int half,
+                                                        int head_dim, double theta, float2* cs) {
+  __shared__ float red[4];
+  const int row = blockIdx.x;
+  const size_t at = (size_t)row * hidden;
+  normalise_row<CPT>(EmbeddedRow{table + (size_t)tokens[row] * hidden, x + at}, gain, out + at, hidden,
+                     eps, red);
+  const int j = threadIdx.x;
+  if (j < half) {
+    const double freq = pow(theta, -2.0 * (double)j / (double)head_dim);
+    const double ang = (double)toks[row].pos * freq;
+    double sn, cn;
+    sincos(ang, &sn, &cn);
+    cs[(size_t)row * half + j] = make_float2((float)cn, (float)sn);
   }
 }
 
@@ -198,37 +220,60 @@ __global__ __launch_bounds__(256) void argmax_reduce_kernel(const float* part_va
   }
 }
 
-// Greedy tree acceptance, one thread per sample: a node is accepted when its
-// parent is and its token is the parent's greedy successor; the deepest
-// accepted node (lowest index on ties) ends the accepted branch.
-__global__ void accept_kernel(const SampleInfo* samples, int batch, const int32_t* tokens,
-                              const int32_t* parents, const TokInfo* toks, const int32_t* argmax,
-                              int32_t* accepted_len, int32_t* next_token,
-                              int32_t* accepted_nodes) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
+// Greedy tree acceptance, one block per sample, thread i = node i.  A node is
+// accepted when on its whole branch every node below the root carries its
+// parent's greedy successor, and no proper ancestor is the EOS token (eos = -1:
+// none); the deepest accepted node (lowest index on ties) ends the accepted
+// branch, and the next token is its greedy successor, or -1 after EOS.  With the
+// ancestor sets at hand that is two ballots, a mask test and a maximum (a thread
+// that walks its sample's nodes, each a chain of dependent loads, took 9 us at 4
+// nodes, 34 at 64 and 59 for 64 samples of 64).
+__global__ __launch_bounds__(kMaxTree) void accept_kernel(const SampleInfo* samples,
+                                                          const int32_t* tokens, const int32_t* parents,
+                                                          const TokInfo* toks, const uint64_t* anc,
+                                                          const int32_t* argmax, int eos,
+                                                          int32_t* accepted_len, int32_t* next_token,
+                                                          int32_t* accepted_nodes) {
+  static_assert(kMaxTree == 64 * kAncWords, "one wave per ancestor word");
+  __shared__ uint64_t ok[kAncWords], end[kAncWords];
+  __shared__ int wave_best[kAncWords];
+  const int b = blockIdx.x, i = threadIdx.x, w = i >> 6;
   const SampleInfo s = samples[b];
-  NodeSet acc;
-  acc.clear();
-  acc.add(0);
-  int best = 0, best_depth = 0;
-  for (int i = 1; i < s.ntok; ++i) {
-    const int row = s.tok0 + i;
-    const int p = parents[row];
-    if (acc.has(p) && tokens[row] == argmax[s.tok0 + p]) {
-      acc.add(i);
-      const int d = toks[row].depth;
-      if (d > best_depth) { best_depth = d; best = i; }
-    }
+  const bool live = i < s.ntok;
+  const int row = s.tok0 + (live ? i : 0);
+  const int tok = tokens[row], depth = toks[row].depth;
+  const int parent = live && i > 0 ? parents[row] : 0;
+  uint64_t set[kAncWords];
+#pragma unroll
+  for (int k = 0; k < kAncWords; ++k) set[k] = anc[(size_t)row * kAncWords + k];
+  const uint64_t ok_w = __ballot(live && (i == 0 || tok == argmax[s.tok0 + parent]));
+  const uint64_t end_w = __ballot(live && tok == eos);
+  if ((i & 63) == 0) {
+    ok[w] = ok_w;
+    end[w] = end_w;
   }
-  accepted_len[b] = best_depth;
-  next_token[b] = argmax[s.tok0 + best];
+  __syncthreads();
+  bool acc = live;
+#pragma unroll
+  for (int k = 0; k < kAncWords; ++k) {
+    const uint64_t above = k == w ? set[k] & ~(1ull << (i & 63)) : set[k];
+    acc = acc && (set[k] & ~ok[k]) == 0 && (above & end[k]) == 0;
+  }
+  int best = acc ? depth * kMaxTree + (kMaxTree - 1 - i) : -1;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) best = max(best, __shfl_xor(best, m));
+  if ((i & 63) == 0) wave_best[w] = best;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kAncWords; ++k) best = max(best, wave_best[k]);      // the root is accepted
+  const int len = best / kMaxTree, node = kMaxTree - 1 - best % kMaxTree;
+  const bool on_branch = live && ((anc[(size_t)(s.tok0 + node) * kAncWords + w] >> (i & 63)) & 1ull);
   int32_t* out = accepted_nodes + (size_t)b * kMaxTree;
-  for (int d = best_depth + 1; d < kMaxTree; ++d) out[d] = -1;
-  int node = best;
-  for (int d = best_depth; d >= 0; --d) {
-    out[d] = node;
-    node = (node > 0) ? parents[s.tok0 + node] : 0;
+  if (on_branch) out[depth] = i;       // the branch has one node per depth 0 .. len
+  if (i > len) out[i] = -1;
+  if (i == 0) {
+    accepted_len[b] = len;
+    next_token[b] = tokens[s.tok0 + node] == eos ? -1 : argmax[s.tok0 + node];
   }
 }
 
@@ -293,31 +338,40 @@ hipError_t launch_tree_meta(const SampleInfo* samples, int batch, const int32_t*
   return hipGetLastError();
 }
 
-hipError_t launch_rope_table(const TokInfo* toks, int n, int head_dim, float theta, float2* cs,
-                             hipStream_t s) {
-  const int half = head_dim / 2;
-  const int total = n * half;
-  rope_table_kernel<<<(total + 255) / 256, 256, 0, s>>>(toks, n, half, head_dim, (double)theta, cs);
-  return hipGetLastError();
+namespace {
+
+// Call `go` with the chunks per thread (an integral_constant) of a row of
+// `hidden` columns.
+template <class F>
+void with_chunks(int hidden, F&& go) {
+  switch ((hidden + 1023) / 1024) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3:
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 5: case 6: case 7:
+    case 8: go(std::integral_constant<int, 8>{}); break;
+    default: go(std::integral_constant<int, 0>{}); break;
+  }
 }
 
-hipError_t launch_embed(const int32_t* tokens, const bf16* table, float* x, int n, int hidden,
-                        hipStream_t s) {
-  embed_kernel<<<n, 256, 0, s>>>(tokens, table, x, hidden);
+}  // namespace
+
+hipError_t launch_row_front(const TokInfo* toks, const int32_t* tokens, const bf16* table,
+                            const bf16* gain, float* x, bf16* out, int n, int hidden, float eps,
+                            int head_dim, float theta, float2* cs, hipStream_t s) {
+  with_chunks(hidden, [&](auto c) {
+    row_front_kernel<decltype(c)::value><<<n, 256, 0, s>>>(toks, tokens, table, gain, x, out, hidden, eps,
+                                                           head_dim / 2, head_dim, (double)theta, cs);
+  });
   return hipGetLastError();
 }
 
 hipError_t launch_rmsnorm(const float* x, const bf16* gain, bf16* out, int n, int hidden,
                           float eps, hipStream_t s) {
-  switch ((hidden + 1023) / 1024) {
-    case 1: rmsnorm_kernel<1><<<n, 256, 0, s>>>(x, gain, out, hidden, eps); break;
-    case 2: rmsnorm_kernel<2><<<n, 256, 0, s>>>(x, gain, out, hidden, eps); break;
-    case 3:
-    case 4: rmsnorm_kernel<4><<<n, 256, 0, s>>>(x, gain, out, hidden, eps); break;
-    case 5: case 6: case 7:
-    case 8: rmsnorm_kernel<8><<<n, 256, 0, s>>>(x, gain, out, hidden, eps); break;
-    default: rmsnorm_kernel<0><<<n, 256, 0, s>>>(x, gain, out, hidden, eps); break;
-  }
+  with_chunks(hidden, [&](auto c) {
+    rmsnorm_kernel<decltype(c)::value><<<n, 256, 0, s>>>(x, gain, out, hidden, eps);
+  });
   return hipGetLastError();
 }
 
@@ -328,11 +382,11 @@ hipError_t launch_argmax_reduce(const float* part_val, const int32_t* part_idx, 
 }
 
 hipError_t launch_accept(const SampleInfo* samples, int batch, const int32_t* tokens,
-                         const int32_t* parents, const TokInfo* toks, const int32_t* argmax,
-                         int32_t* accepted_len, int32_t* next_token, int32_t* accepted_nodes,
-                         hipStream_t s) {
-  accept_kernel<<<(batch + 63) / 64, 64, 0, s>>>(samples, batch, tokens, parents, toks, argmax,
-                                                 accepted_len, next_token, accepted_nodes);
+                         const int32_t* parents, const TokInfo* toks, const uint64_t* anc,
+                         const int32_t* argmax, int eos, int32_t* accepted_len, int32_t* next_token,
+                         int32_t* accepted_nodes, hipStream_t s) {
+  accept_kernel<<<batch, kMaxTree, 0, s>>>(samples, tokens, parents, toks, anc, argmax, eos, accepted_len,
+                                           next_token, accepted_nodes);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // Tree acceptance at a sampling temperature (speculative sampling over the
-// draft tree), and greedy acceptance with an end-of-sequence token.
+// draft tree).
 //
 // Speculative decoding is lossless (RLHFSpec Section 2.2: the verified
 // output follows the target model's distribution).  At temperature T > 0
@@ -685,42 +685,6 @@ __global__ __launch_bounds__(NT) void sample_walk_kernel(
   }
 }
 
-// Greedy acceptance with an end-of-sequence token: as the plain greedy rule
-// (a node is accepted when its parent is and its token is the parent's
-// greedy successor; the deepest accepted node, lowest index on ties, ends
-// the branch), except that an accepted EOS node accepts no children and, if
-// it ends the branch, there is no next token.
-__global__ void accept_eos_kernel(const SampleInfo* samples, int batch, const int32_t* tokens,
-                                  const int32_t* parents, const TokInfo* toks, const int32_t* argmax,
-                                  int eos, int32_t* accepted_len, int32_t* next_token,
-                                  int32_t* accepted_nodes) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
-  const SampleInfo s = samples[b];
-  NodeSet open;                                   // accepted and not EOS: may have children
-  open.clear();
-  if (tokens[s.tok0] != eos) open.add(0);
-  int best = 0, best_depth = 0;
-  for (int i = 1; i < s.ntok; ++i) {
-    const int row = s.tok0 + i;
-    const int p = parents[row];
-    if (open.has(p) && tokens[row] == argmax[s.tok0 + p]) {
-      if (tokens[row] != eos) open.add(i);
-      const int d = toks[row].depth;
-      if (d > best_depth) { best_depth = d; best = i; }
-    }
-  }
-  accepted_len[b] = best_depth;
-  next_token[b] = tokens[s.tok0 + best] == eos ? -1 : argmax[s.tok0 + best];
-  int32_t* out = accepted_nodes + (size_t)b * kMaxTree;
-  for (int d = best_depth + 1; d < kMaxTree; ++d) out[d] = -1;
-  int node = best;
-  for (int d = best_depth; d >= 0; --d) {
-    out[d] = node;
-    node = (node > 0) ? parents[s.tok0 + node] : 0;
-  }
-}
-
 }  // namespace
 
 size_t sample_accept_scratch(int batch, int n_tokens, int vocab) {
@@ -742,15 +706,6 @@ hipError_t launch_sample_accept(const SampleInfo* samples, int batch, int n_toke
   sample_walk_kernel<1024><<<batch, 1024, 0, s>>>(samples, tokens, parents, logits, draft_probs,
                                                   uniforms, vocab, inv_t, eos, recs, resid,
                                                   accepted_len, next_token, accepted_nodes);
-  return hipGetLastError();
-}
-
-hipError_t launch_accept_eos(const SampleInfo* samples, int batch, const int32_t* tokens,
-                             const int32_t* parents, const TokInfo* toks, const int32_t* argmax,
-                             int eos, int32_t* accepted_len, int32_t* next_token,
-                             int32_t* accepted_nodes, hipStream_t s) {
-  accept_eos_kernel<<<(batch + 63) / 64, 64, 0, s>>>(samples, batch, tokens, parents, toks, argmax,
-                                                     eos, accepted_len, next_token, accepted_nodes);
   return hipGetLastError();
 }
 
