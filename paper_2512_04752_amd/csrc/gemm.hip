@@ -1021,6 +1021,10 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t s) {
 // rms, and the choice is on average 0.5 % slower than the best one measured.
 GemmPlan plan_gemm(int epi, int M, int N, int K, int n0, int n1, bool norm) {
   if ((epi == EPI_QKV || epi == EPI_GATE_UP) && M <= kFewRows) return GemmPlan{GEMM_FEW_ROWS, 1};
+  // LM head of few rows: the model puts 64 x 64 and 64 x 128 tiles level; in the
+  // step (8B, 4 layers) 64 x 64 is ahead at 4 rows, 647 against 654 us, and at 16,
+  // 1127 against 1131; level at 32 (692); behind at 96, 925 against 904.
+  if (epi == EPI_ARGMAX && M <= 32) return GemmPlan{GEMM_64x64, 1};
   struct Tile {
     GemmShape shape;
     int bm, bn;
