@@ -647,7 +647,7 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
   if (sampled) {
     const float* logits = D.logits ? D.logits : (const float*)(ws + ly.logits);
     HIP_TRY(timed(SPEC_K_ACCEPT, s, [&] {
-              return launch_sample_accept(d_si, batch, N, d_toks, d_tok, d_par, logits,
+              return launch_sample_accept(d_si, batch, N, d_toks, d_tok, d_par, logits, d_arg,
                                           samp->draft_probs, samp->uniforms, V, samp->temperature,
                                           samp->eos_token, ws + ly.resid, accepted_len, next_token,
                                           accepted_nodes, s);

@@ -189,17 +189,18 @@ int64_t kv_transfer_chunks(int count, int head_dim);
 hipError_t launch_kv_transfer(bool to_buffer, const MigrateInfo* info, int n, int64_t wg_per_slab,
                               int tok_total, bf16* pool, bf16* buf, int n_layers, int n_kv_heads,
                               int head_dim, hipStream_t s);
-// Speculative sampling over the trees (temperature > 0): per-row log-sum-exp
-// of logits / T, then one work-group per sample walks its tree.
+// Speculative sampling over the trees (temperature > 0): every node's decision,
+// then one work-group per sample walks its tree.  argmax: each row's greedy token.
 // Scratch of launch_sample_accept: per-node decisions and one fp64 vocabulary
 // row per sample.
 size_t sample_accept_scratch(int batch, int n_tokens, int vocab);
 hipError_t launch_sample_accept(const SampleInfo* samples, int batch, int n_tokens,
                                 const TokInfo* toks, const int32_t* tokens,
                                 const int32_t* parents, const float* logits,
-                                const float* draft_probs, const float* uniforms, int vocab,
-                                float temperature, int eos, void* scratch, int32_t* accepted_len,
-                                int32_t* next_token, int32_t* accepted_nodes, hipStream_t s);
+                                const int32_t* argmax, const float* draft_probs,
+                                const float* uniforms, int vocab, float temperature, int eos,
+                                void* scratch, int32_t* accepted_len, int32_t* next_token,
+                                int32_t* accepted_nodes, hipStream_t s);
 hipError_t launch_compact(const SampleInfo* samples, int batch, bf16* kv_pool, int n_layers,
                           int n_kv_heads, int head_dim, const int32_t* accepted_len,
                           const int32_t* accepted_nodes, int32_t* new_seq_lens, hipStream_t s);

@@ -397,3 +397,30 @@ def test_full_shape_sampled(name, T):
         assert path[0] == 0 and all(pars[path[k + 1]] == path[k] for k in range(L))
         assert 0 <= int(nxt[b]) < w.cfg.vocab
     release(ver, W_dev)
+
+
+@pytest.mark.parametrize("kids", [1, 8, 9, 63, 64, 65, 128, 255])
+def test_tiny_sampled_child_counts(kids):
+    """A node's children around the edges of its child list: the last child
+    decides without a further total (1, 8), rejections go on on the stored row
+    (9 and more), and the list spans words of 64 nodes.  Sample 0 is a star;
+    in sample 1 the nodes alternate between the root and node 1."""
+    cfg, w, W_cpu, W_dev, ver = tiny_setup(seed=11, batch=8, extra_cap=256, sampling=True)
+    n1 = min(256, 2 * kids + 1)
+    parents = [[-1] + [0] * kids, [-1, 0] + [i % 2 for i in range(2, n1)]]
+    trees = [([w.trees[b][0][0]] + [0] * (len(p) - 1), p) for b, p in enumerate(parents)]
+    ids, lens = [0, 1], w.seq_lens.tolist()[:2]
+    q_all = fill_tokens_by_level(ver, ids, trees, lens, 1.0, mix=0.02, seed=120 + kids, anti=True)
+    N = sum(len(t[0]) for t in trees)
+    U = uniforms_for(N, 130 + kids)
+    U[:, 0] = U_MAX                                 # a child is accepted only where q R < P
+    dbg = ver.debug_buffers(N, logits=True)
+    acc, nxt, nodes = ver.verify_sampled(ids, trees, lens, 1.0, -1, q_all,
+                                         torch.from_numpy(U).cuda(), debug=dbg)
+    torch.cuda.synchronize()
+    out = {"logits": dbg["logits"].cpu(), "accepted_len": acc.cpu().tolist(),
+           "next_token": nxt.cpu().tolist(), "nodes": nodes.cpu()}
+    exact, excused, accepted, rejected = check_sampled(trees, out, q_all, U, 1.0, -1)
+    say(f"  kids {kids}: exact {exact}, excused {excused}, accepted {accepted}, rejected {rejected}")
+    assert exact >= 1 and rejected >= 1
+    release(ver, W_dev)
