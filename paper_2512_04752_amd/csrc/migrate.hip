@@ -14,14 +14,28 @@
 // the grid is ordered [layer, K/V][sample][head][chunk], the work-group
 // decodes its run once (a binary search over the samples' work-group prefix),
 // then streams the chunk with every load of a thread in flight before its
-// stores.  The copy is HBM-bound: 2 bytes moved per byte of K/V.
+// stores.  The copy is HBM-bound: 2 bytes moved per byte of K/V, each touched
+// once, so loads and stores are non-temporal and pass through L2 without
+// displacing one another.  Chunks are small (8 KB, two units per thread), which
+// measured fastest; presumably a mix of short-lived waves keeps loads and stores
+// both in flight, where 16 units per thread are a burst of either.  TB/s moved,
+// pack / unpack of 16 samples (8B shape, 32 layers) and of 64 (8 layers, median
+// 300 tokens):
+//   64 KB chunks, cached           5.1 / 5.1   5.1 / 5.1
+//   64 KB, non-temporal (whole pass, pack and unpack)  5.1
+//   32 KB, non-temporal (whole pass)                   3.7
+//   16 KB, cached                  5.2 / 5.2   5.2 / 5.1
+//   16 KB, non-temporal stores     5.4 / 5.3   5.5 / 5.2
+//   16 KB, non-temporal            5.8 / 5.6   5.7 / 5.4
+//    8 KB, non-temporal            6.2 / 5.9   5.9 / 5.7
+//    4 KB, non-temporal            5.9 / 5.9   5.3 / 5.3
 #include "common.h"
 
 namespace spec {
 
 namespace {
 
-constexpr int kChunk = 4096;               // 16-byte units per work-group (64 KB)
+constexpr int kChunk = 512;                // 16-byte units per work-group (8 KB)
 constexpr int kPer = kChunk / 256;         // units per thread
 
 template <bool TO_BUFFER>
@@ -54,12 +68,12 @@ __global__ __launch_bounds__(256) void kv_transfer_kernel(const MigrateInfo* inf
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const int64_t u = u0 + threadIdx.x + 256 * k;
-    if (u < units) v[k] = src[u];
+    if (u < units) v[k] = __builtin_nontemporal_load(src + u);
   }
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const int64_t u = u0 + threadIdx.x + 256 * k;
-    if (u < units) dst[u] = v[k];
+    if (u < units) __builtin_nontemporal_store(v[k], dst + u);
   }
 }
 

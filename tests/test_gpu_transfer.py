@@ -128,3 +128,28 @@ def test_full_pack_matches_oracle_llama8b():
     buf = gpu_pack(src, ids, begin, end)
     ks, vs = views(src, ids)
     assert torch.equal(buf.cpu().view(torch.int16), oracle.transfer.pack(ks, vs, begin, end))
+
+
+@pytest.mark.parametrize("cfg,edge", [(wl.LLAMA_8B, 32), (wl.TINY, 64)], ids=["hd128", "hd64"])
+def test_runs_around_a_work_groups_chunk(cfg, edge):
+    """Runs that end one token before, at and one token after a whole number of
+    work-group chunks (8 KB: 32 tokens of head dim 128, 64 of 64): bitwise the
+    oracle's buffer, and the unpacked ranges the source's."""
+    cfg = dataclasses.replace(cfg, n_layers=1)
+    counts = [1, edge - 1, edge, edge + 1, 2 * edge, 2 * edge + 1, edge // 2]
+    begin = [3 * j for j in range(len(counts))]
+    end = [b + n for b, n in zip(begin, counts)]
+    caps = [e + 2 for e in end]
+    ids = list(range(len(counts)))
+    say(f"chunk edges, head dim {cfg.head_dim}: counts {counts}")
+    src, dst = random_pool(cfg, caps, 41), random_pool(cfg, caps, 42)
+    buf = gpu_pack(src, ids, begin, end)
+    ks, vs = views(src, ids)
+    assert torch.equal(buf.cpu().view(torch.int16), oracle.transfer.pack(ks, vs, begin, end))
+    want_k, want_v = views(dst, ids)
+    sv.spec_kv_unpack(dst, ids, begin, end, buf)
+    torch.cuda.synchronize()
+    oracle.transfer.unpack(buf.cpu().view(torch.int16), want_k, want_v, begin, end)
+    got_k, got_v = views(dst, ids)
+    for a, b in zip(got_k + got_v, want_k + want_v):
+        assert torch.equal(a, b)
