@@ -335,7 +335,10 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
 // B0 of the next step in the last phase, so the LDS rows of a half are free one
 // phase after their read and take the step after next: phases 0 .. 3 load A1
 // (next step), B0, A0, B1 (step after next), two wave-loads per wave each, and
-// every load has five phases (2.1 of 2.6 thousand cycles) to arrive.
+// every load has five phases (2.1 of 2.6 thousand cycles) to arrive.  Group 1's
+// reads of phase p are complete at the barrier that ends its phase, and group 0
+// is then still in phase p + 1; B0 of step 0, read in front of phase 0 and
+// refilled in phase 1, is waited for where it is read.
 template <int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_256x256_kernel(GemmArgs a) {
   constexpr int BM = 256, BN = 256, ROWB = 128, STAGE = (BM + BN) * ROWB, BOFF = BM * ROWB;
@@ -459,6 +462,7 @@ __global__ __launch_bounds__(512, 2) void gemm_256x256_kernel(GemmArgs a) {
   phase_barrier();
   if (g == 1) phase_barrier();                   // group 1 runs one barrier behind
   read_b(0, 0, fb0[0]);
+  wait_lds();                                    // step 0 refills these rows one phase early
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
