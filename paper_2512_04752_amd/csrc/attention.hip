@@ -63,7 +63,8 @@ typedef short v4i16 __attribute__((ext_vector_type(4)));
 // compiler does not track an LDS write in flight: it cannot tell which ring
 // stage a load targets, and would make every transposing V read wait for all
 // outstanding loads (vmcnt(0)), which collapses the ring's lookahead.  The
-// rings' own vmcnt waits and barriers order these loads.
+// rings' own vmcnt waits and barriers order these loads.  The s_nop is the wait
+// state that the load needs after a write of M0.
 // Every K/V row is read once per step, so the loads carry the non-temporal
 // policy (nt): the stream passes through L2 without displacing what is
 // re-read (queries, partial states).  Measured on the 8B shape: early-phase
@@ -71,7 +72,8 @@ typedef short v4i16 __attribute__((ext_vector_type(4)));
 // attention (batch 4, 64-node trees) 4.59 -> 4.49 ms.
 __device__ __forceinline__ void load_lds16(const void* g, void* lds) {
   const uint32_t m0 = (uint32_t)(uintptr_t)(lds_char*)lds;
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(m0) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(m0)
+               : "memory", "m0");
 }
 
 // Physical 16-byte chunk of logical chunk c in K row `key`: 16 consecutive

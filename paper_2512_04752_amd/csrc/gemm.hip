@@ -47,9 +47,10 @@ typedef __attribute__((address_space(3))) char lds_char;
 // Direct global -> LDS load of 16 bytes per lane from base + voff to the
 // wave-uniform LDS address `lds` + 16 * lane.  In assembly, so that the
 // compiler does not wait for it at the next LDS read; the kernels' own vmcnt
-// waits and barriers order it.
+// waits and barriers order it.  The s_nop is the wait state that the load needs
+// after a write of M0.
 __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
                : "memory", "m0");
 }
 

@@ -3,7 +3,9 @@ the gfx950 assembly that the compiler makes of them.
 
 Tiles reach LDS by loads that the compiler does not order against LDS reads
 (inline assembly), so the kernels order them with barriers: before a barrier
-that lets other waves refill a tile, this wave's reads of it are complete."""
+that lets other waves refill a tile, this wave's reads of it are complete.  Nor
+does the compiler's hazard pass look inside inline assembly: the loads keep the
+wait state between writing M0 and reading it themselves."""
 
 import os
 import re
@@ -97,3 +99,16 @@ def test_reads_complete_at_every_barrier(gemm, name):
     for kernel, body in of(gemm, name).items():
         at = reads_at_barriers(body)
         assert at and max(at) == 0, (kernel, at)
+
+
+@pytest.mark.parametrize("src", ["gemm.hip", "attention.hip"])
+def test_wait_state_between_m0_and_lds_load(src, tmp_path):
+    """gfx9: an LDS-direct load needs one wait state after a scalar write of M0, which holds its
+    LDS address (the compiler puts an s_nop there for its own loads)."""
+    loads = 0
+    for name, body in kernels(assembly(src, str(tmp_path))).items():
+        for before, ins in zip(body, body[1:]):
+            if "load_lds" in ins:
+                loads += 1
+                assert not re.match(r"s_\w+ m0,", before), (name, before, ins)
+    assert loads > 0
