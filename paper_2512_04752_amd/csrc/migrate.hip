@@ -29,6 +29,8 @@
 //   16 KB, non-temporal            5.8 / 5.6   5.7 / 5.4
 //    8 KB, non-temporal            6.2 / 5.9   5.9 / 5.7
 //    4 KB, non-temporal            5.9 / 5.9   5.3 / 5.3
+#include <algorithm>
+
 #include "common.h"
 
 namespace spec {
@@ -37,13 +39,18 @@ namespace {
 
 constexpr int kChunk = 512;                // 16-byte units per work-group (8 KB)
 constexpr int kPer = kChunk / 256;         // units per thread
+// Work-groups of one launch: HIP holds grid x block, in threads, in 32 bits and
+// cuts a larger grid short without an error (16,793,600 work-groups ran 16,384).
+// At 8 KB a work-group that is 137 GB, 69 GB when every run ends just past a
+// chunk: less than a card can hold, so a larger transfer takes several launches.
+constexpr int64_t kMaxGrid = 0xffffffffll / 256;
 
 template <bool TO_BUFFER>
 __global__ __launch_bounds__(256) void kv_transfer_kernel(const MigrateInfo* info, int n,
-                                                          int64_t wg_per_slab, int tok_total,
-                                                          bf16* pool, bf16* buf, int n_kv_heads,
-                                                          int head_dim) {
-  const int64_t wg = blockIdx.x;
+                                                          int64_t first_wg, int64_t wg_per_slab,
+                                                          int tok_total, bf16* pool, bf16* buf,
+                                                          int n_kv_heads, int head_dim) {
+  const int64_t wg = first_wg + blockIdx.x;
   const int lk = (int)(wg / wg_per_slab);            // layer * 2 + (K=0, V=1)
   const int64_t rem = wg % wg_per_slab;
   // Sample whose work-groups cover `rem`: last j with info[j].wg_prefix <= rem.
@@ -88,15 +95,15 @@ hipError_t launch_kv_transfer(bool to_buffer, const MigrateInfo* info, int n, in
                               int tok_total, bf16* pool, bf16* buf, int n_layers, int n_kv_heads,
                               int head_dim, hipStream_t s) {
   if (wg_per_slab == 0) return hipSuccess;
-  const int64_t grid = (int64_t)n_layers * 2 * wg_per_slab;
-  if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  if (to_buffer)
-    kv_transfer_kernel<true><<<(unsigned)grid, 256, 0, s>>>(info, n, wg_per_slab, tok_total, pool,
-                                                            buf, n_kv_heads, head_dim);
-  else
-    kv_transfer_kernel<false><<<(unsigned)grid, 256, 0, s>>>(info, n, wg_per_slab, tok_total, pool,
-                                                             buf, n_kv_heads, head_dim);
-  return hipGetLastError();
+  const int64_t total = (int64_t)n_layers * 2 * wg_per_slab;
+  const auto kernel = to_buffer ? kv_transfer_kernel<true> : kv_transfer_kernel<false>;
+  for (int64_t first = 0; first < total; first += kMaxGrid) {
+    const int64_t grid = std::min(kMaxGrid, total - first);
+    kernel<<<(unsigned)grid, 256, 0, s>>>(info, n, first, wg_per_slab, tok_total, pool, buf, n_kv_heads,
+                                          head_dim);
+    if (const hipError_t e = hipGetLastError()) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace spec

@@ -153,3 +153,24 @@ def test_runs_around_a_work_groups_chunk(cfg, edge):
     got_k, got_v = views(dst, ids)
     for a, b in zip(got_k + got_v, want_k + want_v):
         assert torch.equal(a, b)
+
+
+def test_transfer_of_more_work_groups_than_a_launch_holds():
+    """One token each of 16,400 samples with 1,024 (layer, K/V, head) runs of 128 bytes: 16,793,600
+    work-groups, past the 16,777,215 of 256 threads that one launch can hold.  The buffer is the
+    pool with the samples moved inside layer and K/V; unpacking it elsewhere gives the pool back."""
+    cfg = dataclasses.replace(wl.TINY, n_layers=64, n_kv_heads=8, n_heads=8, head_dim=64)
+    n = 16400
+    assert n * cfg.n_layers * 2 * cfg.n_kv_heads > 0xffffffff // 256
+    say(f"transfer of {n} one-token samples")
+    src, dst = random_pool(cfg, [1] * n, 5), random_pool(cfg, [1] * n, 6)
+    ids, begin, end = list(range(n)), [0] * n, [1] * n
+    buf = gpu_pack(src, ids, begin, end)
+    shape = (n, cfg.n_layers, 2, cfg.n_kv_heads, cfg.head_dim * 2 // 8)
+    blocks = lambda p: p.buf[:buf.numel()].view(torch.int64).view(shape)
+    assert torch.equal(buf.view(torch.int64).view(shape[1], 2, n, *shape[3:]),
+                       blocks(src).permute(1, 2, 0, 3, 4))
+    assert not torch.equal(blocks(dst), blocks(src))
+    sv.spec_kv_unpack(dst, ids, begin, end, buf)
+    torch.cuda.synchronize()
+    assert torch.equal(blocks(dst), blocks(src))
