@@ -360,6 +360,13 @@ enum {
 int spec_profile_begin(int32_t kernel_class, int32_t max_launches);
 int spec_profile_end(float* total_ms, int32_t* launches);
 
+/* How a verify step of n_tokens rows runs one of its products (kernel_class
+ * SPEC_K_GEMM_QKV, _O, _GATE_UP, _DOWN or SPEC_K_LM_HEAD; host arithmetic, for
+ * tests and measurement): rows and columns of its output tile and its K
+ * splits.  The few-rows kernel reports a tile of 16 columns and 0 rows. */
+int spec_gemm_plan(const spec_model_config* cfg, int32_t kernel_class, int32_t n_tokens,
+                   int32_t* tile_rows, int32_t* tile_cols, int32_t* splits);
+
 #ifdef __cplusplus
 }
 #endif

@@ -13,6 +13,7 @@ from .binding import (  # noqa: F401
     SpecError,
     Weights,
     lib,
+    spec_gemm_plan,
     spec_kv_alloc,
     spec_kv_bytes,
     spec_kv_commit,

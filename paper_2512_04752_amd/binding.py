@@ -29,7 +29,7 @@ EXPORTS = ("spec_kv_bytes", "spec_kv_alloc", "spec_kv_free", "spec_kv_sample_lay
            "spec_profile_begin", "spec_profile_end", "spec_kv_transfer_bytes", "spec_kv_pack",
            "spec_kv_unpack", "spec_cost_model_create", "spec_cost_model_free", "spec_cost_predict",
            "spec_cost_model_stats", "spec_select_draft_count", "spec_workspace_bytes_sampled",
-           "spec_verify_sampled", "spec_verify_noalloc")
+           "spec_verify_sampled", "spec_verify_noalloc", "spec_gemm_plan")
 SPEC_NOALLOC_SCRATCH_BYTES = 320 << 20
 
 
@@ -118,11 +118,12 @@ def lib():
     L.spec_last_error.restype = ctypes.c_char_p
     L.spec_profile_begin.argtypes = [c_int32, c_int32]
     L.spec_profile_end.argtypes = [POINTER(c_float), i32p]
+    L.spec_gemm_plan.argtypes = [POINTER(spec_model_config), c_int32, c_int32, i32p, i32p, i32p]
     for name in ("spec_kv_alloc", "spec_kv_free", "spec_kv_sample_layout", "spec_verify",
                  "spec_kv_commit", "spec_profile_begin", "spec_profile_end", "spec_kv_pack",
                  "spec_kv_unpack", "spec_cost_model_create", "spec_cost_model_free",
                  "spec_cost_model_stats", "spec_select_draft_count", "spec_verify_sampled",
-                 "spec_verify_noalloc"):
+                 "spec_verify_noalloc", "spec_gemm_plan"):
         getattr(L, name).restype = c_int32
     _lib = L
     return L
@@ -418,3 +419,13 @@ def spec_profile_end():
     ms, n = c_float(), c_int32()
     _check(lib().spec_profile_end(ctypes.byref(ms), ctypes.byref(n)))
     return ms.value, n.value
+
+
+def spec_gemm_plan(cfg, kernel_class, n_tokens):
+    """(tile rows, tile columns, K splits) of a product ("gemm_qkv", "gemm_o", "gemm_gate_up",
+    "gemm_down", "lm_head") of a verify step of n_tokens rows; (0, 16, 1) on the few-rows kernel."""
+    c = make_config(cfg)
+    rows, cols, splits = c_int32(), c_int32(), c_int32()
+    _check(lib().spec_gemm_plan(ctypes.byref(c), KERNEL_CLASS[kernel_class], n_tokens,
+                                ctypes.byref(rows), ctypes.byref(cols), ctypes.byref(splits)))
+    return rows.value, cols.value, splits.value

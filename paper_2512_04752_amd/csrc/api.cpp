@@ -133,6 +133,19 @@ WsLayout ws_layout(const spec_model_config* c, int64_t max_batch, int64_t max_to
   return L;
 }
 
+// The plan of one product (SPEC_K_*) of a verify step of n rows.
+GemmPlan product_plan(const spec_model_config* c, int kind, int n) {
+  const int q = c->n_heads * c->head_dim, kv = c->n_kv_heads * c->head_dim;
+  switch (kind) {
+    case SPEC_K_GEMM_QKV: return plan_gemm(EPI_QKV, n, q + 2 * kv, c->hidden, q, kv, false);
+    case SPEC_K_GEMM_O: return plan_gemm(EPI_RESID, n, c->hidden, q, c->hidden, 0, true);
+    case SPEC_K_GEMM_GATE_UP:
+      return plan_gemm(EPI_GATE_UP, n, 2 * c->ffn, c->hidden, c->ffn, c->ffn, false);
+    case SPEC_K_GEMM_DOWN: return plan_gemm(EPI_RESID, n, c->hidden, c->ffn, c->hidden, 0, true);
+    default: return plan_gemm(EPI_ARGMAX, n, c->vocab, c->hidden, c->vocab, 0, false);
+  }
+}
+
 // Process-wide kernel timing state (measurement only).
 struct Profiler {
   bool on = false;
@@ -582,11 +595,9 @@ int verify_impl(const spec_model_config* cfg, const spec_weights* w, spec_kv* kv
     if (!fused) HIP_TRY(launch_rmsnorm(d_x, (const bf16*)gain, d_h, N, H, cfg->rms_eps, s), "rmsnorm");
     return SPEC_OK;
   };
-  const GemmPlan p_qkv = plan_gemm(EPI_QKV, N, (nq + 2 * nkv) * hd, H, nq * hd, nkv * hd, false);
-  const GemmPlan p_o = plan_gemm(EPI_RESID, N, H, nq * hd, H, 0, true);
-  const GemmPlan p_gate_up = plan_gemm(EPI_GATE_UP, N, 2 * F, H, F, F, false);
-  const GemmPlan p_down = plan_gemm(EPI_RESID, N, H, F, H, 0, true);
-  const GemmPlan p_head = plan_gemm(EPI_ARGMAX, N, V, H, V, 0, false);
+  const GemmPlan p_qkv = product_plan(cfg, SPEC_K_GEMM_QKV, N), p_o = product_plan(cfg, SPEC_K_GEMM_O, N),
+                 p_gate_up = product_plan(cfg, SPEC_K_GEMM_GATE_UP, N),
+                 p_down = product_plan(cfg, SPEC_K_GEMM_DOWN, N), p_head = product_plan(cfg, SPEC_K_LM_HEAD, N);
   for (int l = 0; l < L; ++l) {
     GemmArgs g = ga;
     g.plan = p_qkv;
@@ -850,5 +861,28 @@ SPEC_API int spec_profile_end(float* total_ms, int32_t* launches) {
   for (auto e : g_prof.ev) (void)hipEventDestroy(e);
   g_prof.ev.clear();
   g_prof.count = 0;
+  return SPEC_OK;
+}
+
+SPEC_API int spec_gemm_plan(const spec_model_config* cfg, int32_t kernel_class, int32_t n_tokens,
+                            int32_t* tile_rows, int32_t* tile_cols, int32_t* splits) {
+  g_err.clear();
+  if (!cfg || !tile_rows || !tile_cols || !splits) return fail(SPEC_ERR_INVALID, "null argument");
+  std::string why;
+  if (!config_ok(cfg, &why)) return fail(SPEC_ERR_UNSUPPORTED, "%s", why.c_str());
+  if (kernel_class != SPEC_K_GEMM_QKV && kernel_class != SPEC_K_GEMM_O && kernel_class != SPEC_K_GEMM_GATE_UP &&
+      kernel_class != SPEC_K_GEMM_DOWN && kernel_class != SPEC_K_LM_HEAD)
+    return fail(SPEC_ERR_INVALID, "kernel class %d is not a product", kernel_class);
+  if (n_tokens < 1) return fail(SPEC_ERR_INVALID, "n_tokens must be >= 1");
+  const GemmPlan p = product_plan(cfg, kernel_class, n_tokens);
+  *splits = p.splits;
+  switch (p.shape) {
+    case GEMM_FEW_ROWS: *tile_rows = 0, *tile_cols = 16; break;
+    case GEMM_64x64: *tile_rows = 64, *tile_cols = 64; break;
+    case GEMM_64x128: *tile_rows = 64, *tile_cols = 128; break;
+    case GEMM_128x128: *tile_rows = 128, *tile_cols = 128; break;
+    case GEMM_256x128: *tile_rows = 256, *tile_cols = 128; break;
+    case GEMM_256x256: *tile_rows = 256, *tile_cols = 256; break;
+  }
   return SPEC_OK;
 }
