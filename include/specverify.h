@@ -196,7 +196,7 @@ typedef struct {
 } spec_sampling;
 
 /* Workspace bytes spec_verify_sampled needs at temperature > 0 (the logits
- * [N][vocab] fp32, per-row log-sum-exp and a [batch][vocab] fp64 residual on
+ * [N][vocab] fp32, the nodes' decisions and a [batch][vocab] fp64 residual on
  * top of spec_workspace_bytes); 0 if an argument is invalid.  At temperature
  * 0 spec_workspace_bytes suffices. */
 size_t spec_workspace_bytes_sampled(const spec_model_config* cfg, int32_t max_batch,

@@ -322,11 +322,13 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
 // all waves read, then all multiply.)  Measured on the gate/up
 // product of the 8B shape (28672 x 4096, weights from HBM), us at 512 / 1024 /
 // 4096 rows: plain ring 150 / 253 / 878, these phases with the same 32x32x16
-// instructions 124 / 232 / 768.  The loop then issues MFMAs in 97 % of its
-// cycles and the card's power limit sets the clock (about 1.4 GHz), so energy
-// per product counts: 16x16x32 instructions, whose accumulator traffic per flop
-// is half, sustain 2.06 against 1.83 PFLOP/s in a loop of MFMAs alone, and take
-// the same product to 106 / 213 / 699 us (1.38 PFLOP/s at 4096 rows).
+// instructions 124 / 232 / 768.  The clock then falls with the load (counters
+// over the whole kernel at 4096 rows: 1.8 of 2.4 GHz, the matrix cores busy in
+// 81 % of its cycles; presumably the card's power limit), so energy per product
+// counts: 16x16x32 instructions, whose accumulator traffic per flop is half,
+// sustain 2.06 against 1.83 PFLOP/s in a loop of MFMAs alone, and take the same
+// product to 106 / 213 / 699 us (1.38 PFLOP/s at 4096 rows; 634 to 699 from one
+// card to another).
 
 // 256 x 256 tiles, 64-wide K steps in two stages of 64 KB.  Group g holds rows
 // 128 g .., wave q = wave % 4 of it columns 64 q ..: 128 x 64 per wave.  Every
@@ -336,7 +338,7 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
 // B0 of the next step in the last phase, so the LDS rows of a half are free one
 // phase after their read and take the step after next: phases 0 .. 3 load A1
 // (next step), B0, A0, B1 (step after next), two wave-loads per wave each, and
-// every load has five phases (2.1 of 2.6 thousand cycles) to arrive.  Group 1's
+// every load has five phases (of 512 MFMA cycles, both groups') to arrive.  Group 1's
 // reads of phase p are complete at the barrier that ends its phase, and group 0
 // is then still in phase p + 1; B0 of step 0, read in front of phase 0 and
 // refilled in phase 1, is waited for where it is read.
@@ -592,9 +594,10 @@ __global__ __launch_bounds__(512, 2) void gemm_256x128_kernel(GemmArgs a) {
 // Up to some 256 rows a product is bound by the bytes its CUs can take in: the
 // weights from HBM (about 6 TB/s) and, as often as there are weight tiles, the
 // rows from L2 (about 13 TB/s over the chip), so the tile is chosen for the
-// fewest of both with every CU loading: 64 x 64 while the rows are few (its 64
-// KB leave two work-groups on a CU, each covering the other's waits), then
-// 64 x 128 (72 KB, two) and 128 x 128 (128 KB, one).  Deeper rings, and rings in
+// fewest of both with every CU loading: 64 x 64 for narrow products (8B O and
+// down, all of 1B's, up to 64 rows; its 64 KB leave two work-groups on a CU, each
+// covering the other's waits), 64 x 128 (72 KB, also two) for wide ones (8B q/k/v
+// and gate/up from 5 rows) and 128 x 128 (128 KB, one) beyond 64 rows.  Deeper rings, and rings in
 // which some waves load only rows and the others only weights, were no faster.
 // An unsplit product starts its K loop at a step that depends on the weight
 // tile (and wraps around): with all CUs at the same K of rows 2^n bytes apart
@@ -1021,14 +1024,18 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t s) {
 // others' step shrinks to `alone` of it when few CUs work (less L2 traffic, and a
 // higher clock).  `fixed` is each round's prologue and epilogue.  An unsplit
 // residual product leaves its RMSNorm to a launch of its own (5 us); a reduction
-// takes it along.  Fitted to 1381 measurements of the five tiles and their splits
-// on the 8B and 1B shapes' products at 1 to 4096 rows, weights from HBM: 3.4 %
-// rms, and the choice is on average 0.5 % slower than the best one measured.
+// takes it along.  Launched back to back on the 8B and 1B shapes' products, 1 to
+// 4096 rows, weights from HBM, the five tiles and their splits (3285 times taken)
+// need about 3 us a launch more than the model says (17 % rms; 9 % with the 3 us
+// added), and the one chosen is on average 1.0 % slower than the best of them, at
+// worst 18 % (1B O at 640 rows, 22.1 against 18.7 us).  Storing the logits has no
+// term (8B head at 1024 rows 751 -> 841 us): with it the choice is 0.3 % off.
 GemmPlan plan_gemm(int epi, int M, int N, int K, int n0, int n1, bool norm) {
   if ((epi == EPI_QKV || epi == EPI_GATE_UP) && M <= kFewRows) return GemmPlan{GEMM_FEW_ROWS, 1};
-  // LM head of few rows: the model puts 64 x 64 and 64 x 128 tiles level; in the
-  // step (8B, 4 layers) 64 x 64 is ahead at 4 rows, 647 against 654 us, and at 16,
-  // 1127 against 1131; level at 32 (692); behind at 96, 925 against 904.
+  // LM head of few rows: the model puts 64 x 64 and 64 x 128 tiles level.  Whole
+  // steps with either, us: 8B, 4 layers, 641 or 649 at 4 rows, 661 or 671 at 16,
+  // 674 or 683 at 32, 702 or 709 at 48, 737 or 736 at 64, 915 or 888 at 96; 1B, 8
+  // layers, level to 48 rows (594 or 594 at 32), 660 or 653 at 64, 801 or 786 at 96.
   if (epi == EPI_ARGMAX && M <= 32) return GemmPlan{GEMM_64x64, 1};
   struct Tile {
     GemmShape shape;
