@@ -1034,8 +1034,8 @@ GemmPlan plan_gemm(int epi, int M, int N, int K, int n0, int n1, bool norm) {
   if ((epi == EPI_QKV || epi == EPI_GATE_UP) && M <= kFewRows) return GemmPlan{GEMM_FEW_ROWS, 1};
   // LM head of few rows: the model puts 64 x 64 and 64 x 128 tiles level.  Whole
   // steps with either, us: 8B, 4 layers, 641 or 649 at 4 rows, 661 or 671 at 16,
-  // 674 or 683 at 32, 702 or 709 at 48, 737 or 736 at 64, 915 or 888 at 96; 1B, 8
-  // layers, level to 48 rows (594 or 594 at 32), 660 or 653 at 64, 801 or 786 at 96.
+  // 674 or 683 at 32, 702 or 709 at 48, 738 or 736 at 64, 915 or 888 at 96; 1B, 8
+  // layers, level to 48 rows (595 or 594 at 32), 661 or 654 at 64, 801 or 786 at 96.
   if (epi == EPI_ARGMAX && M <= 32) return GemmPlan{GEMM_64x64, 1};
   struct Tile {
     GemmShape shape;
