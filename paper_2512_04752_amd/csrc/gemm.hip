@@ -324,7 +324,7 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, f32x4 (&acc)[MB
 // 4096 rows: plain ring 150 / 253 / 878, these phases with the same 32x32x16
 // instructions 124 / 232 / 768.  The clock then falls with the load (counters
 // over the whole kernel at 4096 rows: 1.8 of 2.4 GHz, the matrix cores busy in
-// 81 % of its cycles; presumably the card's power limit), so energy per product
+// 83 % of its cycles; presumably the card's power limit), so energy per product
 // counts: 16x16x32 instructions, whose accumulator traffic per flop is half,
 // sustain 2.06 against 1.83 PFLOP/s in a loop of MFMAs alone, and take the same
 // product to 106 / 213 / 699 us (1.38 PFLOP/s at 4096 rows; 634 to 699 from one
